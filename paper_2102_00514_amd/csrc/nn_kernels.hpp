@@ -201,123 +201,6 @@ __global__ __launch_bounds__(kThreads) void k_conv_mfma(ConvArgs a) {
       }
 }
 
-// ---------------------------------------------------------------------------
-// Inference form of a dilated residual layer, h' = h + relu(b + sum_k W_k h(.
-// + (k - 1) d)), for C channels in and out (C = 128 or 256).  A block takes
-// 128 positions -- whole windows, so every tap that stays inside its window
-// stays inside the tile -- and all C output channels.  Its input tile is read
-// from HBM once, rounded to BF16 and staged position-major in LDS, where one
-// 8-byte read gives an MFMA B fragment (4 consecutive channels at one
-// position); the packed weights give A fragments the same way.  The residual
-// is added from the unrounded FP32 input, and only h' is written (the ReLU
-// part alone is kept by the training form, for the backward pass).
-// Wave w computes rows 32 w .. 32 w + 31 of each 128-row chunk, all 128
-// positions: 2 x 8 blocks of 16 x 16 x 16 BF16 MFMA, FP32 accumulation.
-// grid ceil(N / 128); requires 128 % Lpos == 0 and N % Lpos == 0.
-// ---------------------------------------------------------------------------
-struct ResidualArgs {
-  int N, Lpos, dil;     // positions, positions per window, dilation
-  const short* Wt;      // [C][3][C] BF16 bits: Wt[(m * 3 + k) * C + c] = bf16(W[m][c][k])
-  const float* bias;    // [C]
-  const float* h;       // [C][N] layer input
-  float* out;           // [C][N] layer output h'
-};
-
-constexpr int kResP = 128;   // positions per block of k_residual_mfma
-
-// Wt[(m * 3 + k) * C + c] = bf16(W[(m * C + c) * 3 + k]); grid ceil(3 C^2 / 256).
-__global__ __launch_bounds__(256) void k_pack_residual(const float* W, int C, short* Wt) {
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= int64_t(3) * C * C) return;
-  const int c = int(e % C), k = int((e / C) % 3);
-  const int64_t m = e / (int64_t(3) * C);
-  Wt[e] = to_bf16(W[(m * C + c) * 3 + k]);
-}
-
-template <int C>
-__global__ __launch_bounds__(256) void k_residual_mfma(ResidualArgs a) {
-  static_assert(C % 128 == 0, "128-row chunks");
-  constexpr int CP = C + 8;   // LDS row pitch (BF16): rows 16 B apart in bank order
-  __shared__ __align__(16) short Hs[kResP][CP];
-  const int t = threadIdx.x, wv = t >> 6, ln = t & 63;
-  const int64_t p0 = int64_t(blockIdx.x) * kResP;
-  // stage the tile: each thread moves 4 channels x 4 positions per pass
-  // (float4 reads along positions, one 8-byte LDS write per position)
-  for (int b = t; b < (C / 4) * (kResP / 4); b += 256) {
-    const int cb = b / (kResP / 4), pb = b - cb * (kResP / 4);
-    const int c = 4 * cb, p = 4 * pb;
-    const int64_t pp = p0 + p;
-    float v[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (pp + 3 < a.N) {
-        const float4 x = ld4(a.h + int64_t(c + i) * a.N + pp);
-        v[i][0] = x.x; v[i][1] = x.y; v[i][2] = x.z; v[i][3] = x.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[i][j] = pp + j < a.N ? a.h[int64_t(c + i) * a.N + pp + j] : 0.f;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bf16x4 w;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = to_bf16(v[i][j]);
-      *reinterpret_cast<bf16x4*>(&Hs[p + j][c]) = w;
-    }
-  }
-  __syncthreads();
-  const int kq = 4 * (ln >> 4), lr = ln & 15;
-  for (int m0 = 0; m0 < C; m0 += 128) {
-    const int mrow = m0 + 32 * wv + lr;   // A-fragment row of block i: mrow + 16 i
-    f32x4 acc[2][8];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < 3; ++k) {
-      const int off = (k - 1) * a.dil;
-      // per position block j: the tap's LDS row and whether it stays in the window
-      int row[8];
-      bool live[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int pl = 16 * j + lr, q = pl % a.Lpos + off;
-        live[j] = q >= 0 && q < a.Lpos;
-        row[j] = live[j] ? pl + off : pl;
-      }
-#pragma unroll 2
-      for (int c0 = 0; c0 < C; c0 += 16) {
-        bf16x4 af[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          af[i] = *reinterpret_cast<const bf16x4*>(a.Wt + (int64_t(mrow + 16 * i) * 3 + k) * C + c0 + kq);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          bf16x4 bv = *reinterpret_cast<const bf16x4*>(&Hs[row[j]][c0 + kq]);
-          if (!live[j]) bv = bf16x4{0, 0, 0, 0};
-#pragma unroll
-          for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bv, acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = m0 + 32 * wv + 16 * i + kq + q;
-        const float bm = a.bias[m];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int64_t p = p0 + 16 * j + lr;
-          if (p >= a.N) continue;
-          const int64_t o = int64_t(m) * a.N + p;
-          a.out[o] = a.h[o] + fmaxf(acc[i][j][q] + bm, 0.f);
-        }
-      }
-  }
-}
-
 // Weight gradient partials: part[z][m][r] = sum over the z-th chunk of
 // positions of D[m][p] B(r, p), with r = Kr the bias column (B = 1).
 // grid (ceil((Kr + 1) / 64), ceil(M / 64), chunks).
@@ -535,6 +418,251 @@ __global__ void k_scatter(WindowTable tab, const float* o, int64_t w0, int n, in
     const double v = double(mu[i] + sigma[i] * o[size_t(u * nx + i) * n * L + size_t(b) * L + j]);
     mean[slot * nx + i] = v;
     if (k == 1) mean[(slot - 1) * nx + i] = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Inference form of the whole network on the matrix cores (width C = 128 or
+// 256, whole windows in a tile of 128 positions): features, embedding, every
+// residual layer, head, and the scatter into the trajectory, in one kernel.
+// Windows do not interact, so a block takes kNetP positions (whole windows)
+// through all layers: the FP32 residual stream stays in registers, in the
+// MFMA result layout that the next layer's epilogue needs again, and only its
+// BF16 rounding goes through LDS, position-major, as the next layer's B
+// operand.  HBM sees the measurements and the trajectory alone; one kernel per
+// layer moved the stream through HBM twice per layer (C = 128, four residual
+// layers, 32,768 windows of 16 positions: 1.39 ms a call, 0.35 now).
+// Bound: the BF16 products (206 GFLOP), their LDS reads (each wave reads the
+// whole tile for its C / 4 rows) close behind.
+//
+// Products are 16 x 16 x 16 BF16 MFMA with FP32 accumulation, reduction in
+// order of (tap, channel): operands of k_conv_mfma, element for element.  Two
+// of its 16-deep steps are stored side by side -- channel 16 h + 4 g + j of a
+// group of 32 sits at 8 g + 4 h + j (net_col) -- so that one 16-byte read
+// feeds both, of the LDS tile and of the weights, which are packed in the
+// order in which the lanes take them (k_pack_net).
+// ---------------------------------------------------------------------------
+constexpr int kNetP = 128;   // positions per block
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
+
+__host__ __device__ __forceinline__ int net_col(int c) {
+  return (c & ~31) | ((c & 12) << 1) | ((c & 16) >> 2) | (c & 3);
+}
+
+// 16-row tiles and 32-deep steps of a packed weight matrix of M rows and Kr columns.
+__host__ __device__ __forceinline__ int net_steps(int Kr) { return (Kr + 31) / 32; }
+__host__ __device__ __forceinline__ int64_t net_words(int M, int Kr) {
+  return int64_t((M + 15) / 16) * net_steps(Kr) * 512;
+}
+
+// A weight matrix [M][cin][K] as BF16 fragments: word 8 l + e of (row tile mt,
+// step s) is row 16 mt + l % 16, reduction index r = 32 s + 16 (e / 4) +
+// 4 (l / 16) + e % 4, zero past the matrix.  Reduction order: taps outermost
+// when tap_major (r = k cin + c), else r = c K + k.
+struct PackArgs {
+  const float* W;
+  int M, cin, K, tap_major;
+  short* out;
+};
+__global__ __launch_bounds__(256) void k_pack_net(PackArgs a) {
+  const int Kr = a.cin * a.K, steps = net_steps(Kr);
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= net_words(a.M, Kr)) return;
+  const int e = int(i & 7), l = int(i >> 3) & 63;
+  const int64_t t = i >> 9;
+  const int s = int(t % steps), m = int(t / steps) * 16 + (l & 15);
+  const int r = 32 * s + 16 * (e >> 2) + 4 * (l >> 4) + (e & 3);
+  float v = 0.f;
+  if (m < a.M && r < Kr) {
+    const int c = a.tap_major ? r % a.cin : r / a.K, k = a.tap_major ? r / a.cin : r - c * a.K;
+    v = a.W[(int64_t(m) * a.cin + c) * a.K + k];
+  }
+  a.out[i] = to_bf16(v);
+}
+
+struct NetArgs {
+  WindowTable tab;
+  const double* y;
+  double* mean;
+  int64_t w0, n;                 // first window, windows of this launch
+  int ny, W, P, nx, Lpos, hidden;
+  const short *we, *wr, *wh;     // packed embedding, residual layers, head
+  const float *be, *bh;          // biases of the embedding and the head
+  const float* br;               // bias of the first residual layer; the next one's br_stride later
+  int64_t br_stride;
+  const float *mu, *sigma;
+};
+
+template <int C>
+__global__ __launch_bounds__(256, C == 128 ? 2 : 1) void k_net_mfma(NetArgs a) {
+  static_assert(C % 128 == 0, "whole 32-row pairs of tiles per wave");
+  constexpr int RT = C / 64;     // 16-row tiles per wave
+  constexpr int NT = kNetP / 16;  // 16-position tiles
+  constexpr int CP = C + 8;      // LDS row pitch (BF16): rows 16 B apart in bank order
+  __shared__ __align__(16) short Hs[kNetP + 1][CP];   // last row: zeros, for taps outside the window
+  const int t = threadIdx.x, wv = t >> 6, ln = t & 63, g = ln >> 4, lr = ln & 15;
+  const int64_t p0 = int64_t(blockIdx.x) * kNetP;     // of this launch's positions
+  const int64_t N = a.n * a.Lpos;
+  for (int c = t; c < CP; c += 256) Hs[kNetP][c] = 0;
+
+  f32x4 h[RT][NT], acc[RT][NT];
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // acc += W[rows of this wave][steps s0 ..] x Hs[row[j]], columns 0 .. 32 n
+  auto product = [&](const short* w, int steps, int s0, int n, const int (&row)[NT]) {
+    const short* wp = w + (int64_t(wv * RT) * steps + s0) * 512 + ln * 8;
+#pragma unroll 2
+    for (int s = 0; s < n; ++s) {
+      bf16x8 af[RT];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) af[i] = *reinterpret_cast<const bf16x8*>(wp + (int64_t(i) * steps + s) * 512);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Hs[row[j]][32 * s + 8 * g]);
+        const bf16x4 b0 = __builtin_shufflevector(b, b, 0, 1, 2, 3), b1 = __builtin_shufflevector(b, b, 4, 5, 6, 7);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          const bf16x4 a0 = __builtin_shufflevector(af[i], af[i], 0, 1, 2, 3);
+          const bf16x4 a1 = __builtin_shufflevector(af[i], af[i], 4, 5, 6, 7);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b1, acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  };
+  // the stream's BF16 rounding, position-major: 4 consecutive channels per write
+  auto publish = [&] {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        bf16x4 v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = to_bf16(h[i][j][q]);
+        *reinterpret_cast<bf16x4*>(&Hs[16 * j + lr][net_col((wv * RT + i) * 16 + 4 * g)]) = v;
+      }
+  };
+
+  // embedding, in column blocks of C of its reduction (one for 2 ny P <= C)
+  const int Kr = 2 * a.ny * a.P, se = net_steps(Kr);
+  int row[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) row[j] = 16 * j + lr;
+  clear();
+  for (int kb = 0; kb < Kr; kb += C) {
+    const int cols = min(C, 32 * (se - kb / 32));
+    if (kb > 0) __syncthreads();
+    // columns past the reduction of the last step
+    for (int e = t; e < kNetP * 32; e += 256) {
+      const int c = cols - 32 + (e & 31);
+      if (kb + c >= Kr) Hs[e >> 5][net_col(c)] = 0;
+    }
+    const int per = a.ny * a.P;
+    for (int e = t; e < kNetP * per; e += 256) {
+      const int p = e / per, q = e - p * per, s = q % a.ny, k = q / a.ny;
+      const int c0 = 2 * s * a.P + k - kb, c1 = c0 + a.P;   // sine, cosine columns
+      float sf = 0.f, cf = 0.f;
+      if (p0 + p < N) {
+        const int64_t w = a.w0 + (p0 + p) / a.Lpos;
+        const int tr = a.tab.track[w];
+        const int64_t m0 = a.tab.meas_off[tr], T = a.tab.meas_off[tr + 1] - m0;
+        const int64_t st = min(int64_t(a.tab.start[w]) + ((p0 + p) % a.Lpos) * a.P + k, T);
+        double sv, cv;
+        sincos(a.y[(m0 + st - 1) * a.ny + s], &sv, &cv);
+        sf = float(sv);
+        cf = float(cv);
+      }
+      if (c0 >= 0 && c0 < C) Hs[p][net_col(c0)] = to_bf16(sf);
+      if (c1 >= 0 && c1 < C) Hs[p][net_col(c1)] = to_bf16(cf);
+    }
+    __syncthreads();
+    product(a.we, se, kb / 32, cols / 32, row);
+  }
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float b = a.be[(wv * RT + i) * 16 + 4 * g + q];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) h[i][j][q] = fmaxf(acc[i][j][q] + b, 0.f);
+    }
+  __syncthreads();
+  publish();
+  __syncthreads();
+
+  // residual layers: h += relu(b + sum over taps)
+  constexpr int SC = C / 32;
+  for (int l = 0; l < a.hidden; ++l) {
+    const short* w = a.wr + int64_t(l) * net_words(C, 3 * C);
+    const int dil = 1 << l;
+    clear();
+    for (int k = 0; k < 3; ++k) {
+      const int off = (k - 1) * dil;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const int pl = 16 * j + lr, q = pl % a.Lpos + off;
+        row[j] = q >= 0 && q < a.Lpos ? pl + off : kNetP;
+      }
+      product(w, 3 * SC, k * SC, SC, row);
+    }
+    const float* bias = a.br + l * a.br_stride;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float b = bias[(wv * RT + i) * 16 + 4 * g + q];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) h[i][j][q] += fmaxf(acc[i][j][q] + b, 0.f);
+      }
+    __syncthreads();
+    publish();
+    __syncthreads();
+  }
+
+  // head: each wave takes 32 positions and every output row; step k of a track
+  // comes from window min((k - 1) / W, n_w - 1) of it, slot 0 from step 1
+  const int M = a.P * a.nx;
+  for (int mt = 0; mt * 16 < M; ++mt) {
+    f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < SC; ++s) {
+      const bf16x8 af = *reinterpret_cast<const bf16x8*>(a.wh + (int64_t(mt) * SC + s) * 512 + ln * 8);
+      const bf16x4 a0 = __builtin_shufflevector(af, af, 0, 1, 2, 3), a1 = __builtin_shufflevector(af, af, 4, 5, 6, 7);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(&Hs[32 * wv + 16 * j + lr][32 * s + 8 * g]);
+        const bf16x4 b0 = __builtin_shufflevector(b, b, 0, 1, 2, 3), b1 = __builtin_shufflevector(b, b, 4, 5, 6, 7);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0, o[j], 0, 0, 0);
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b1, o[j], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int64_t p = p0 + 32 * wv + 16 * j + lr;
+      if (p >= N) continue;
+      const int64_t w = a.w0 + p / a.Lpos;
+      const int tr = a.tab.track[w];
+      const int64_t m0 = a.tab.meas_off[tr], T = a.tab.meas_off[tr + 1] - m0;
+      const int64_t k0 = int64_t(a.tab.start[w]) + (p % a.Lpos) * a.P;
+      const int first = a.tab.first[tr], nw = a.tab.first[tr + 1] - first;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = mt * 16 + 4 * g + q;
+        if (m >= M) continue;
+        const int u = m / a.nx, i = m - u * a.nx;
+        const int64_t k = k0 + u;
+        if (k > T || first + min((k - 1) / a.W, int64_t(nw - 1)) != w) continue;
+        const float out = o[j][q] + a.bh[m];
+        const double v = double(a.mu[i] + a.sigma[i] * out);
+        double* x = a.mean + (m0 + tr + k) * a.nx + i;
+        *x = v;
+        if (k == 1) x[-a.nx] = v;
+      }
+    }
   }
 }
 

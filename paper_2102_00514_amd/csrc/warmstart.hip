@@ -76,8 +76,9 @@ struct ws_net {
   float *dh[2] = {nullptr, nullptr}, *dz[2] = {nullptr, nullptr};
   float *part = nullptr, *loss_part = nullptr, *loss = nullptr;
   int* bad_index = nullptr;   // set by the batch gather when an index is out of range
-  short* wt16 = nullptr;      // residual weights packed for k_residual_mfma ([hidden][3 C^2] BF16)
-  bool res_fast = false;      // the inference form runs k_residual_mfma (C = 128 or 256, 128 % Lpos == 0)
+  short* wt16 = nullptr;      // BF16 weights packed for k_net_mfma: embedding, residual layers, head
+  bool net_fused = false;     // the inference form runs k_net_mfma (C = 128 or 256, 128 % Lpos == 0)
+  bool net_packed = false;    // wt16 holds the current parameters
   int64_t part_floats = 0;
   int* win_track = nullptr;
   int* win_start = nullptr;
@@ -160,9 +161,12 @@ struct ws_net {
     A_(&loss_part, 1024);
     A_(&loss, 1);
     if (e == hipSuccess) e = alloc(reinterpret_cast<void**>(&bad_index), sizeof(int), allocs);
-    res_fast = (c.width == 128 || c.width == 256) && wsn::kResP % Lpos == 0 && c.hidden > 0;
-    if (res_fast && e == hipSuccess)
-      e = alloc(reinterpret_cast<void**>(&wt16), sizeof(short) * 3 * size_t(c.width) * c.width * c.hidden, allocs);
+    net_fused = (c.width == 128 || c.width == 256) && wsn::kNetP % Lpos == 0;
+    if (net_fused && e == hipSuccess) {
+      int64_t words = 0;
+      for (const auto& L : layers) words += wsn::net_words(L.cout, L.cin * L.K);
+      e = alloc(reinterpret_cast<void**>(&wt16), sizeof(short) * size_t(words), allocs);
+    }
     if (e != hipSuccess)
       return fail(e == hipErrorOutOfMemory ? WS_ENOMEM : WS_EDEVICE, hip_msg(e, "device allocation"));
     std::vector<float> ones(c.nx, 1.f);
@@ -210,15 +214,6 @@ struct ws_net {
     }
     for (int l = 1; l <= Hn; ++l) {
       const LayerSpec& L = layers[l];
-      if (mfma && res_fast) {
-        // the packed weights come from pack_residual(), run before the batch loop
-        const wsn::ResidualArgs r{N, Lpos, L.dil, wt16 + size_t(l - 1) * 3 * L.cout * L.cout, theta + L.b_off,
-                                  H[l - 1], H[l]};
-        const dim3 grid(unsigned((N + wsn::kResP - 1) / wsn::kResP));
-        if (L.cout == 128) hipLaunchKernelGGL(wsn::k_residual_mfma<128>, grid, dim3(256), 0, stream, r);
-        else hipLaunchKernelGGL(wsn::k_residual_mfma<256>, grid, dim3(256), 0, stream, r);
-        continue;
-      }
       wsn::ConvArgs a{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, H[l - 1], n, false),
                       A[l], H[l], H[l - 1], nullptr};
       conv<wsn::kEpiResidual>(a, mfma);
@@ -229,13 +224,50 @@ struct ws_net {
     conv<wsn::kEpiLinear>(a, mfma);
   }
 
-  // BF16 tap-major copies of the residual weights for k_residual_mfma
-  void pack_residual() {
-    for (int l = 1; l <= cfg.hidden; ++l) {
+  // BF16 copies of the weights for k_net_mfma, made again when they have changed
+  void pack_net() {
+    if (net_packed) return;
+    short* out = wt16;
+    for (size_t l = 0; l < layers.size(); ++l) {
       const LayerSpec& L = layers[l];
-      const int64_t cnt = int64_t(3) * L.cout * L.cout;
-      hipLaunchKernelGGL(wsn::k_pack_residual, dim3(unsigned((cnt + 255) / 256)), dim3(256), 0, stream,
-                         static_cast<const float*>(theta + L.w_off), L.cout, wt16 + size_t(l - 1) * cnt);
+      const int64_t words = wsn::net_words(L.cout, L.cin * L.K);
+      hipLaunchKernelGGL(wsn::k_pack_net, dim3(unsigned((words + 255) / 256)), dim3(256), 0, stream,
+                         wsn::PackArgs{theta + L.w_off, L.cout, L.cin, L.K, l > 0 ? 1 : 0, out});
+      out += words;
+    }
+    net_packed = true;
+  }
+
+  // trajectory of every planned window through k_net_mfma (no workspace)
+  void trajectory_fused(const double* d_y, double* d_mean) {
+    pack_net();
+    const LayerSpec &LE = layers.front(), &LH = layers.back();
+    wsn::NetArgs a{};
+    a.tab = table();
+    a.y = d_y;
+    a.mean = d_mean;
+    a.ny = cfg.ny;
+    a.W = cfg.window;
+    a.P = cfg.patch;
+    a.nx = cfg.nx;
+    a.Lpos = Lpos;
+    a.hidden = cfg.hidden;
+    a.we = wt16;
+    a.wr = a.we + wsn::net_words(LE.cout, LE.cin * LE.K);
+    a.wh = a.wr + cfg.hidden * wsn::net_words(cfg.width, 3 * cfg.width);
+    a.be = theta + LE.b_off;
+    a.bh = theta + LH.b_off;
+    a.br = theta + layers[1].b_off;     // without residual layers not read
+    a.br_stride = layers[1].weights() + layers[1].cout;
+    a.mu = mu;
+    a.sigma = sigma;
+    constexpr int64_t kMost = int64_t(1) << 20;   // windows per launch (grid size)
+    for (int64_t w0 = 0; w0 < n_windows; w0 += kMost) {
+      a.w0 = w0;
+      a.n = std::min(kMost, n_windows - w0);
+      const dim3 grid(unsigned((a.n * Lpos + wsn::kNetP - 1) / wsn::kNetP));
+      if (cfg.width == 128) hipLaunchKernelGGL(wsn::k_net_mfma<128>, grid, dim3(256), 0, stream, a);
+      else hipLaunchKernelGGL(wsn::k_net_mfma<256>, grid, dim3(256), 0, stream, a);
     }
   }
 
@@ -379,6 +411,7 @@ ws_status ws_set_params(ws_t h, const float* params, int64_t n) {
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_m, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_v, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  h->net_packed = false;
   if (e != hipSuccess) return h->fail(WS_EDEVICE, hip_msg(e, "parameter upload"));
   h->step = 0;
   return WS_OK;
@@ -487,6 +520,7 @@ ws_status ws_train_step(ws_t h, const float* d_x, const float* d_lab, int64_t n_
   hipLaunchKernelGGL(wsn::k_adam, dim3(unsigned((h->n_params + 255) / 256)), dim3(256), 0, h->stream, h->theta,
                      static_cast<const float*>(h->grad), h->adam_m, h->adam_v, h->n_params, opt->lr, opt->beta1,
                      opt->beta2, opt->eps, c1, c2);
+  h->net_packed = false;
   ws_status s = launch_status(h, "training step");
   if (s != WS_OK || !loss_out) return s;
   const hipError_t e = hipMemcpyAsync(loss_out, h->loss, sizeof(float), hipMemcpyDeviceToHost, h->stream);
@@ -535,8 +569,11 @@ static ws_status trajectory(ws_t h, const double* d_y, double* d_mean, bool mfma
   if (!h) return WS_ESTATE;
   if (!h->n_windows) return h->fail(WS_ESTATE, "no tracks planned (ws_set_tracks)");
   if (!d_y || !d_mean) return h->fail(WS_EINVAL, "null device pointer");
+  if (mfma && h->net_fused) {
+    h->trajectory_fused(d_y, d_mean);
+    return launch_status(h, "trajectory");
+  }
   const int W = h->cfg.window;
-  if (mfma && h->res_fast) h->pack_residual();
   for (int64_t w0 = 0; w0 < h->n_windows; w0 += h->cfg.max_batch) {
     const int nb = int(std::min<int64_t>(h->cfg.max_batch, h->n_windows - w0));
     const int64_t cnt = int64_t(nb) * W;
