@@ -8,6 +8,8 @@
 // stored upper-packed (sym_index order) in HBM and full in LDS.
 #pragma once
 
+#include <type_traits>
+
 #include "elements.hpp"
 #include "slot_kernels.hpp"
 
@@ -21,7 +23,17 @@ constexpr int ld() { return N + 1; }           // LDS row length (odd: spreads b
 template <int N>
 constexpr int mat_words() { return N * ld<N>(); }
 
-PKS_DEV int lane() { return int(threadIdx.x); }
+// The lane, opaque to the optimiser at every call: a routine computes its LDS
+// addresses when it runs.  Left visible, the addresses of every routine of a
+// kernel are hoisted out of its slot loop and spill to scratch around each
+// factorisation: k_dn_forward_down_backward_up 1.63 ms (416 bytes of scratch
+// per lane) against 1.24 and k_dn_forward_up 1.57 against 1.13 at 65,537 slots.
+// The smoothing kernels, which factorise nothing, are 12 % slower by it.
+PKS_DEV int lane() {
+  int l = int(threadIdx.x);
+  asm volatile("" : "+v"(l));
+  return l;
+}
 PKS_DEV void wsync() { __syncthreads(); }     // workgroups are a single wave
 
 // ---------------------------------------------------------------------------
@@ -65,61 +77,8 @@ PKS_DEV void mm_valu(const R* A, const R* B, const R* C0, R sgn, R* C) {
   wsync();
 }
 
-// C = C0 + sgn * op(A) op(B), op(A) M x K, op(B) K x NC.  C may alias C0 but
-// not A or B.  C0 may be null (zero).  FP64 20 x 20 x 20 (the full-state
-// blocks): v_mfma_f64_16x16x4f64 on the product padded to 32 x 32, 2 x 2
-// output tiles, 5 steps of 4 along the reduction; lane l feeds A[l % 16][l /
-// 16] and B[l / 16][l % 16] and receives D[4 q + l / 16][l % 16], q = 0..3.
-// Two LDS words per 2048 flops against six per eight multiply-adds on the
-// VALU (mm_valu, measured against it by libdense_probe.so).  Other shapes and
-// FP32: mm_valu.
-template <int LDN, int M, int K, int NC, bool TA, bool TB, typename R>
-PKS_DEV void mm(const R* A, const R* B, const R* C0, R sgn, R* C) {
-  constexpr int L = ld<LDN>();
-  if constexpr (sizeof(R) == 8 && M == 20 && K == 20 && NC == 20) {
-    // Every LDS read is unconditional and issued before the first MFMA: rows
-    // and columns past 19 of the padded operands read row or column 19 and
-    // are replaced by zero with a select, and result elements past 19 (and
-    // their C0 reads) go to column 20 of the rows, the unused padding of the
-    // LDS layout, instead of being skipped behind branches.
-    const int r = lane() & 15, kq = lane() >> 4;
-    double av[5][2], bv[5][2];
-    PKS_UNROLL for (int ks = 0; ks < 5; ++ks) {
-      const int k = 4 * ks + kq;   // < 20
-      PKS_UNROLL for (int t = 0; t < 2; ++t) {
-        const int i = 16 * t + r, ic = i < 20 ? i : 19;
-        const double a = double(TA ? A[k * L + ic] : A[ic * L + k]);
-        const double b = double(TB ? B[ic * L + k] : B[k * L + ic]);
-        av[ks][t] = i < 20 ? a : 0.0;
-        bv[ks][t] = i < 20 ? b : 0.0;
-      }
-    }
-    int at[2][2][4];
-    R c0[2][2][4];
-    PKS_UNROLL for (int ti = 0; ti < 2; ++ti)
-      PKS_UNROLL for (int tj = 0; tj < 2; ++tj)
-        PKS_UNROLL for (int q = 0; q < 4; ++q) {
-          const int i = 16 * ti + 4 * q + kq, j = 16 * tj + r;
-          at[ti][tj][q] = (i < 20 && j < 20) ? i * L + j : (i < 20 ? i : i - 20) * L + 20;
-          c0[ti][tj][q] = C0 ? C0[at[ti][tj][q]] : R(0);
-        }
-    f64x4 acc[2][2];
-    PKS_UNROLL for (int i = 0; i < 2; ++i) PKS_UNROLL for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-    PKS_UNROLL for (int ks = 0; ks < 5; ++ks)
-      PKS_UNROLL for (int ti = 0; ti < 2; ++ti)
-        PKS_UNROLL for (int tj = 0; tj < 2; ++tj)
-          acc[ti][tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks][ti], bv[ks][tj], acc[ti][tj], 0, 0, 0);
-    PKS_UNROLL for (int ti = 0; ti < 2; ++ti)
-      PKS_UNROLL for (int tj = 0; tj < 2; ++tj)
-        PKS_UNROLL for (int q = 0; q < 4; ++q) C[at[ti][tj][q]] = c0[ti][tj][q] + sgn * R(acc[ti][tj][q]);
-    wsync();
-    return;
-  }
-  mm_valu<LDN, M, K, NC, TA, TB, R>(A, B, C0, sgn, C);
-}
-
 // y = y0 + sgn * op(A) x, op(A) M x K.  y may alias y0 but not x.
-template <int LDN, int M, int K, bool TA, typename R>
+template <int LDN, int M, int K, bool TA, typename R, bool SYNC = true>
 PKS_DEV void mv(const R* A, const R* x, const R* y0, R sgn, R* y) {
   constexpr int L = ld<LDN>();
   for (int i = lane(); i < M; i += kWave) {
@@ -127,7 +86,126 @@ PKS_DEV void mv(const R* A, const R* x, const R* y0, R sgn, R* y) {
     PKS_UNROLL for (int k = 0; k < K; ++k) s = fma(TA ? A[k * L + i] : A[i * L + k], x[k], s);
     y[i] = (y0 ? y0[i] : R(0)) + sgn * s;
   }
-  wsync();
+  if constexpr (SYNC) wsync();
+}
+
+// C = C0 + sgn * op(A) op(B), op(A) M x K, op(B) K x NC.  C may alias C0 but
+// not A or B.  C0 may be null (zero).  FP64: on the matrix cores; FP32:
+// mm_valu.
+//
+// 20 x K x 20 (the full-state blocks): 16 x 16 of the result with
+// v_mfma_f64_16x16x4f64 and its last four rows and columns with
+// v_mfma_f64_4x4x4f64, whose four independent 4 x 4 blocks are the row (or
+// column) tiles of the strip.  Lane l feeds A[l % 16][l / 16] and B[l / 16][l %
+// 16] to both, so the strips use the operand registers of the 16 x 16 block
+// and one more row and column of four; it receives D[4 q + l / 16][l % 16], q =
+// 0..3, of the large form and, of block b = l / 4 % 4 of the small one,
+// D_b[l / 16][l % 4].  Four large and twelve small instructions per 16 of the
+// reduction take 560 cycles of the matrix core for K = 20; padding the product
+// to 32 x 32 (20 large ones) took 1280, and stored and read back 2.3 times the
+// result words.  One product alone on a wave: 1992 cycles before, 1080 now.
+// Other shapes (multiples of four): small form alone, four result tiles per
+// instruction.
+//
+// x, y: y = y0 + ysgn * op(A) x beside the product (x null: none), y0 may be
+// null or y, but not x.  On the matrix cores the vector is one more column
+// tile (every column of it the vector), which shares the product's operand
+// reads and latency; alone (mv) it took 520 cycles of one wave.
+template <int LDN, int M, int K, int NC, bool TA, bool TB, typename R>
+PKS_DEV void mm(const R* A, const R* B, const R* C0, R sgn, R* C, const R* x = nullptr, const R* y0 = nullptr,
+                R ysgn = R(1), R* y = nullptr) {
+  constexpr int L = ld<LDN>();
+  if constexpr (sizeof(R) == 8 && M % 4 == 0 && K % 4 == 0 && NC % 4 == 0) {
+    constexpr int KS = K / 4;
+    const int ln = lane(), kq = ln >> 4, c4 = ln & 3;
+    auto ra = [&](int i, int k) { return double(TA ? A[k * L + i] : A[i * L + k]); };
+    auto rb = [&](int k, int j) { return double(TB ? B[j * L + k] : B[k * L + j]); };
+    if constexpr (M == 20 && NC == 20) {
+      // every LDS read is issued before the first MFMA
+      const int r = ln & 15, b4 = (ln >> 2) & 3;
+      double a16[KS], a4[KS], b16[KS], bs[KS];
+      PKS_UNROLL for (int ks = 0; ks < KS; ++ks) {
+        const int k = 4 * ks + kq;
+        a16[ks] = ra(r, k);
+        b16[ks] = rb(k, r);
+        a4[ks] = ra(16 + c4, k);
+        bs[ks] = rb(k, 16 + c4);
+      }
+      int at[7];
+      R c0[7];
+      PKS_UNROLL for (int q = 0; q < 4; ++q) at[q] = (4 * q + kq) * L + r;
+      at[4] = (4 * b4 + kq) * L + 16 + c4;   // rows 0..15, columns 16..19
+      at[5] = (16 + kq) * L + r;             // rows 16..19, columns 0..15
+      at[6] = (16 + kq) * L + 16 + c4;       // the corner, in every block alike
+      PKS_UNROLL for (int q = 0; q < 7; ++q) c0[q] = C0 ? C0[at[q]] : R(0);
+      double xs[KS], z0 = 0.0, z1 = 0.0, ya = 0.0, yb = 0.0;
+      if (x) {
+        PKS_UNROLL for (int ks = 0; ks < KS; ++ks) xs[ks] = x[4 * ks + kq];
+        if (y0) {
+          z0 = y0[4 * b4 + kq];
+          z1 = y0[16 + kq];
+        }
+      }
+      f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+      double right = 0.0, below = 0.0, corner = 0.0;
+      PKS_UNROLL for (int ks = 0; ks < KS; ++ks) {
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a16[ks], b16[ks], acc, 0, 0, 0);
+        right = __builtin_amdgcn_mfma_f64_4x4x4f64(a16[ks], bs[ks], right, 0, 0, 0);
+        below = __builtin_amdgcn_mfma_f64_4x4x4f64(a4[ks], b16[ks], below, 0, 0, 0);
+        corner = __builtin_amdgcn_mfma_f64_4x4x4f64(a4[ks], bs[ks], corner, 0, 0, 0);
+        if (x) {
+          ya = __builtin_amdgcn_mfma_f64_4x4x4f64(a16[ks], xs[ks], ya, 0, 0, 0);
+          yb = __builtin_amdgcn_mfma_f64_4x4x4f64(a4[ks], xs[ks], yb, 0, 0, 0);
+        }
+      }
+      PKS_UNROLL for (int q = 0; q < 4; ++q) C[at[q]] = c0[q] + sgn * R(acc[q]);
+      C[at[4]] = c0[4] + sgn * R(right);
+      C[at[5]] = c0[5] + sgn * R(below);
+      C[at[6]] = c0[6] + sgn * R(corner);
+      if (x) {
+        y[4 * b4 + kq] = z0 + ysgn * ya;
+        y[16 + kq] = z1 + ysgn * yb;
+      }
+    } else {
+      constexpr int TN = NC / 4, tiles = (M / 4) * TN, G = (tiles + 3) / 4;
+      double acc[G], av[G][KS], bv[G][KS];
+      int at[G];
+      R c0[G];
+      PKS_UNROLL for (int g = 0; g < G; ++g) {
+        // blocks past the last tile compute it once more
+        const int t = 4 * g + ((ln >> 2) & 3), id = t < tiles ? t : tiles - 1;
+        const int i0 = 4 * (id / TN), j0 = 4 * (id % TN);
+        PKS_UNROLL for (int ks = 0; ks < KS; ++ks) {
+          av[g][ks] = ra(i0 + c4, 4 * ks + kq);
+          bv[g][ks] = rb(4 * ks + kq, j0 + c4);
+        }
+        at[g] = (i0 + kq) * L + j0 + c4;
+        c0[g] = C0 ? C0[at[g]] : R(0);
+        acc[g] = 0.0;
+      }
+      static_assert(M <= 16, "row tiles of the vector fit the four blocks");
+      const int iv = 4 * min((ln >> 2) & 3, M / 4 - 1);
+      double ax[KS], xs[KS], z0 = 0.0, ya = 0.0;
+      if (x) {
+        PKS_UNROLL for (int ks = 0; ks < KS; ++ks) {
+          ax[ks] = ra(iv + c4, 4 * ks + kq);
+          xs[ks] = x[4 * ks + kq];
+        }
+        if (y0) z0 = y0[iv + kq];
+      }
+      PKS_UNROLL for (int ks = 0; ks < KS; ++ks) {
+        PKS_UNROLL for (int g = 0; g < G; ++g)
+          acc[g] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[g][ks], bv[g][ks], acc[g], 0, 0, 0);
+        if (x) ya = __builtin_amdgcn_mfma_f64_4x4x4f64(ax[ks], xs[ks], ya, 0, 0, 0);
+      }
+      PKS_UNROLL for (int g = 0; g < G; ++g) C[at[g]] = c0[g] + sgn * R(acc[g]);
+      if (x) y[iv + kq] = z0 + ysgn * ya;
+    }
+    wsync();
+    return;
+  }
+  if (x) mv<LDN, M, K, TA, R, false>(A, x, y0, ysgn, y);
+  mm_valu<LDN, M, K, NC, TA, TB, R>(A, B, C0, sgn, C);
 }
 
 // Value of x in lane `src` (uniform), as a double.
@@ -138,112 +216,430 @@ PKS_DEV double lane_value(double x, int src) {
   return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
 }
 
-// In-place lower Cholesky factor (true diagonal); the upper triangle is
-// cleared.  *ok (LDS) is cleared when a pivot is not positive; the factor then
-// holds NaN, which reaches the convergence statistic.  Lane i keeps row i in
-// registers; column j takes the finished entries of row j from lane j with
-// cross-lane reads, so the whole factorisation touches LDS twice.
+// Left-looking factorisation with the library square root and division, a
+// column at a time in LDS: chol for pivots outside the range of its fast form
+// (not positive, not finite, or so large or small that its residuals would
+// leave the exponent range).
 template <int LDN, int N, typename R>
-PKS_DEV void chol(R* A, int* ok) {
-  static_assert(N <= kWave, "one row per lane");
+PKS_DEV void chol_any(R* A, int* ok) {
   constexpr int L = ld<LDN>();
   const int i = lane();
-  R row[N];
-  PKS_UNROLL for (int k = 0; k < N; ++k) row[k] = i < N ? A[i * L + k] : R(0);
   bool good = true;
-  PKS_UNROLL for (int j = 0; j < N; ++j) {
-    R s0 = row[j], s1 = R(0);
-    PKS_UNROLL for (int t = 0; t < j; ++t) {
-      const R ljt = lane_value(row[t], j);
-      if (t & 1) s1 = fma(-row[t], ljt, s1);
-      else s0 = fma(-row[t], ljt, s0);
+#pragma unroll 1
+  for (int j = 0; j < N; ++j) {
+    R s = R(0);
+    if (i < N) {
+      s = A[i * L + j];
+#pragma unroll 1
+      for (int t = 0; t < j; ++t) s = fma(-A[i * L + t], A[j * L + t], s);
     }
-    const R s = s0 + s1;
-    const R d = lane_value(s, j);               // pivot of column j
+    const R d = R(lane_value(double(s), j));
     good = good && d > R(0);
     const R sd = sqrt(d);
-    row[j] = i == j ? sd : (i > j ? s / sd : R(0));
-  }
-  if (i < N) {
-    PKS_UNROLL for (int k = 0; k < N; ++k) A[i * L + k] = k <= i ? row[k] : R(0);
+    wsync();                                     // row j has been read
+    if (i < N) A[i * L + j] = i == j ? sd : (i > j ? s / sd : R(0));
+    wsync();
   }
   if (i == 0 && !good) *ok = 0;
-  wsync();
 }
 
-// B <- Lc^-1 B (forward substitution), Lc N x N lower, B N x NC; lane per
-// column, the column kept in registers.
-template <int LDN, int N, int NC, typename R>
-PKS_DEV void fwd(const R* Lc, R* B) {
-  constexpr int L = ld<LDN>();
-  for (int c = lane(); c < NC; c += kWave) {
-    R x[N];
-    PKS_UNROLL for (int i = 0; i < N; ++i) x[i] = B[i * L + c];
-    PKS_UNROLL for (int i = 0; i < N; ++i) {
-      R s = x[i];
-      PKS_UNROLL for (int t = 0; t < i; ++t) s = fma(-Lc[i * L + t], x[t], s);
-      x[i] = s / Lc[i * L + i];
+// f(std::integral_constant<int, B>) ... f(<E - 1>): loops whose index selects a
+// cross-lane move, which takes it as an instruction field.
+template <int B, int E, class F>
+PKS_DEV void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// The value of lane SRC of each row of 16 lanes, in every lane of that row
+// (row_newbcast, on the VALU).  Reading a lane through the scalar unit instead
+// stalls its user by about 20 cycles.
+template <int SRC>
+PKS_DEV double row_bcast(double x) { return __builtin_amdgcn_mov_dpp(x, 0x150 + SRC, 0xf, 0xf, true); }
+template <int SRC>
+PKS_DEV float row_bcast(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + SRC, 0xf, 0xf, true));
+}
+
+// A lower-triangular N x N factor in registers, N even, N / 2 <= 16: lane l
+// holds rows l % 16 and l % 16 + N / 2 (the first without its columns past N /
+// 2), every 16 lanes the same, so that an entry reaches all lanes by one
+// row_bcast; lanes l % 16 >= N / 2 repeat row N / 2 - 1 and the last.  The
+// diagonal entries of the two rows stand in dlo and dhi (those of lo and hi are
+// not used), their reciprocals in rlo and rhi.
+template <int N, typename R>
+struct Factor {
+  static constexpr int H = N / 2;
+  static_assert(N % 2 == 0 && H <= 16, "two rows per lane of a row of 16");
+  R lo[H], hi[N], dlo, dhi;
+  double rlo, rhi;
+  static PKS_DEV int row(int l) { return min(l & 15, H - 1); }
+  // entry (K, K) and its reciprocal, in every lane
+  template <int K>
+  PKS_DEV R diag() const { return K < H ? row_bcast<K % H>(dlo) : row_bcast<K % H>(dhi); }
+  template <int K>
+  PKS_DEV double rcp() const { return K < H ? row_bcast<K % H>(rlo) : row_bcast<K % H>(rhi); }
+  template <int LDN>
+  PKS_DEV void load(const R* A) {
+    constexpr int L = ld<LDN>();
+    const int rl = row(lane());
+    const R *a = A + rl * L, *b = a + H * L;
+    PKS_UNROLL for (int k = 0; k < H; ++k) lo[k] = a[k];
+    PKS_UNROLL for (int k = 0; k < N; ++k) hi[k] = b[k];
+    dlo = a[rl];
+    dhi = b[rl + H];
+    rlo = 1.0 / double(dlo);
+    rhi = 1.0 / double(dhi);
+  }
+};
+
+// Multiply-adds whose first factor comes over from another lane of the row of
+// 16 (one instruction each, 5 cycles).  fnma_lanes: acc[u] -= (src of lane LANE
+// + u) * x, u < CNT <= 10; fnma_sum: acc -= sum over u, in order, of (src of
+// lane LANE + u) * x[u].  The two wait states that a lane move needs after its
+// source was written stand at the head of the block, and nothing in the block
+// writes src.
+#define PKS_T(T, d, x, u) "v_fmac_" T "_dpp %" d ", -%[s], %" x " row_newbcast:%[l]+" #u " row_mask:0xf bank_mask:0xf\n\t"
+#define PKS_V1(F, T) F(T, 0)
+#define PKS_V2(F, T) PKS_V1(F, T) F(T, 1)
+#define PKS_V3(F, T) PKS_V2(F, T) F(T, 2)
+#define PKS_V4(F, T) PKS_V3(F, T) F(T, 3)
+#define PKS_V5(F, T) PKS_V4(F, T) F(T, 4)
+#define PKS_V6(F, T) PKS_V5(F, T) F(T, 5)
+#define PKS_V7(F, T) PKS_V6(F, T) F(T, 6)
+#define PKS_V8(F, T) PKS_V7(F, T) F(T, 7)
+#define PKS_V9(F, T) PKS_V8(F, T) F(T, 8)
+#define PKS_V10(F, T) PKS_V9(F, T) F(T, 9)
+#define PKS_O1(c, v) [v0] c(v[0])
+#define PKS_O2(c, v) PKS_O1(c, v), [v1] c(v[1])
+#define PKS_O3(c, v) PKS_O2(c, v), [v2] c(v[2])
+#define PKS_O4(c, v) PKS_O3(c, v), [v3] c(v[3])
+#define PKS_O5(c, v) PKS_O4(c, v), [v4] c(v[4])
+#define PKS_O6(c, v) PKS_O5(c, v), [v5] c(v[5])
+#define PKS_O7(c, v) PKS_O6(c, v), [v6] c(v[6])
+#define PKS_O8(c, v) PKS_O7(c, v), [v7] c(v[7])
+#define PKS_O9(c, v) PKS_O8(c, v), [v8] c(v[8])
+#define PKS_O10(c, v) PKS_O9(c, v), [v9] c(v[9])
+#define PKS_FL(T, u) PKS_T(T, "[v" #u "]", "[x]", u)
+#define PKS_FS(T, u) PKS_T(T, "[a]", "[v" #u "]", u)
+#define PKS_LANES(T, n) \
+  if constexpr (CNT == n) asm("s_nop 1\n\t" PKS_V##n(PKS_FL, T) : PKS_O##n("+v", acc) : [s] "v"(src), [x] "v"(x), [l] "n"(LANE));
+#define PKS_SUM(T, n) \
+  if constexpr (CNT == n) asm("s_nop 1\n\t" PKS_V##n(PKS_FS, T) : [a] "+v"(acc) : [s] "v"(src), PKS_O##n("v", x), [l] "n"(LANE));
+#define PKS_ALL(F, T) \
+  F(T, 1) F(T, 2) F(T, 3) F(T, 4) F(T, 5) F(T, 6) F(T, 7) F(T, 8) F(T, 9) F(T, 10)
+#define PKS_FNMA(R, T)                                                           \
+  template <int LANE, int CNT>                                                   \
+  PKS_DEV void fnma_lanes(R* acc, R src, R x) {                                  \
+    static_assert(CNT >= 1 && CNT <= 10 && LANE + CNT <= 16, "lanes of one row"); \
+    PKS_ALL(PKS_LANES, T)                                                        \
+  }                                                                              \
+  template <int LANE, int CNT>                                                   \
+  PKS_DEV void fnma_sum(R& acc, R src, const R* x) {                             \
+    static_assert(CNT >= 1 && CNT <= 10 && LANE + CNT <= 16, "lanes of one row"); \
+    PKS_ALL(PKS_SUM, T)                                                          \
+  }
+PKS_FNMA(double, "f64")
+PKS_FNMA(float, "f32")
+#undef PKS_FNMA
+
+// Lower Cholesky factor (true diagonal) of the matrix A in LDS, into f and,
+// with store, in place of A, the upper triangle cleared.  *ok (LDS) is cleared
+// when a pivot is not positive; the factor then holds NaN, which reaches the
+// convergence statistic.  Only the lower triangle of A is read.
+//
+// A finished column is applied to the later ones at once, to the next one
+// first: the others (in blocks of fnma_lanes) fill the gaps of the chain from
+// pivot to pivot (sum, broadcast, square root, quotient, product).  The sums
+// of even and odd columns stay apart and are added last.  Entries above the
+// diagonal hold unused values until the factor is stored.  Square root and
+// quotients share one estimate y of 1/sqrt(d): the hardware's (5e-8) after one
+// Newton step (4e-15); with g = d y, g + (d - g^2) y / 2 is the correctly
+// rounded root, and with q = s y, q + (s - q root) y the correctly rounded
+// quotient (Markstein's corrections: what y lacks enters squared), in 9
+// dependent operations where the library root and division took about 30.
+// One factorisation alone on a wave: 9280 cycles before, 4870 now.
+template <int LDN, int N, typename R>
+PKS_DEV void chol(R* A, int* ok, Factor<N, R>& f, bool store) {
+  constexpr int L = ld<LDN>(), H = N / 2;
+  const int ln = lane(), rl = Factor<N, R>::row(ln);
+  const R *Al = A + rl * L, *Ah = Al + H * L;
+  R lodd[H], hodd[N];
+  PKS_UNROLL for (int k = 0; k < H; ++k) {
+    f.lo[k] = Al[k];
+    lodd[k] = R(0);
+  }
+  PKS_UNROLL for (int k = 0; k < N; ++k) {
+    f.hi[k] = Ah[k];
+    hodd[k] = R(0);
+  }
+  f.rlo = f.rhi = 0.0;
+  R dl = R(0), dh = R(0);    // diagonal entries of the two rows
+  // pivots of the fast form lie in [2^-664, 2^664): high words from kLow on
+  constexpr unsigned kLow = 0x16700000u, kSpan = 0x69700000u - kLow;
+  unsigned range = 0u;
+  auto column = [&](auto J) {
+    constexpr int j = decltype(J)::value, i = j > 0 ? j - 1 : 0;
+    constexpr bool low = j < H;
+    // column i applied to column j, and (block) to the later ones of the rows
+    // that have them: part 0 the first rows, 1 the others up to column H, 2 the
+    // others from H on
+    if constexpr (j > 0) {
+      const R l = row_bcast<j % H>(low ? f.lo[i < H ? i : 0] : f.hi[i]);
+      R& ah = i & 1 ? hodd[j] : f.hi[j];
+      ah = fma(-l, f.hi[i], ah);
+      if constexpr (low) {
+        R& al = i & 1 ? lodd[low ? j : 0] : f.lo[low ? j : 0];
+        al = fma(-l, f.lo[i], al);
+      }
     }
-    PKS_UNROLL for (int i = 0; i < N; ++i) B[i * L + c] = x[i];
+    auto block = [&](auto PT) {
+      constexpr int part = decltype(PT)::value;
+      constexpr int end = part < 2 ? H : N, beg = part < 2 ? 0 : H;
+      constexpr int k0 = j + 1 > beg ? j + 1 : beg;
+      if constexpr (j > 0 && k0 < end) {
+        const R src = part < 2 ? f.lo[i < H ? i : 0] : f.hi[i];
+        const R x = part == 0 ? f.lo[i < H ? i : 0] : f.hi[i];
+        R* even = part == 0 ? f.lo : f.hi;
+        R* odd = part == 0 ? lodd : hodd;
+        fnma_lanes<k0 - beg, end - k0>((i & 1 ? odd : even) + k0, src, x);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const R sl = low ? f.lo[low ? j : 0] + lodd[low ? j : 0] : R(0), sh = f.hi[j] + hodd[j];
+    block(std::integral_constant<int, 2>{});
+    const double d = double(row_bcast<j % H>(low ? sl : sh));   // pivot of column j
+    double y = __builtin_amdgcn_rsq(d);
+    block(std::integral_constant<int, 0>{});
+    y = fma(0.5 * y, fma(-d * y, y, 1.0), y);
+    const double g = d * y, hy = 0.5 * y;
+    double qh = double(sh) * y, ql = double(sl) * y;
+    block(std::integral_constant<int, 1>{});
+    const R root = R(fma(fma(-g, g, d), hy, g));
+    const double rt = double(root);
+    // in FP32 the rounding of the root leaves the quotients 2^-24 off: one more correction
+    if constexpr (sizeof(R) == 4) {
+      qh = fma(fma(-qh, rt, double(sh)), y, qh);
+      if constexpr (low) ql = fma(fma(-ql, rt, double(sl)), y, ql);
+    }
+    const double wh = fma(-qh, rt, double(sh)), wl = fma(-ql, rt, double(sl));
+    const unsigned top = static_cast<unsigned>(static_cast<unsigned long long>(__double_as_longlong(d)) >> 32) - kLow;
+    range = top > range ? top : range;
+    qh = fma(wh, y, qh);
+    if constexpr (low) ql = fma(wl, y, ql);
+    if constexpr (low) f.lo[j] = R(ql);
+    f.hi[j] = R(qh);
+    const double er = fma(-rt, y, 1.0);
+    const double rc = fma(sizeof(R) == 4 ? fma(er, er, er) : er, y, y);   // 1 / root
+    const bool own = rl == (low ? j : j - H);
+    if constexpr (low) {
+      f.rlo = own ? rc : f.rlo;
+      dl = own ? root : dl;
+    } else {
+      f.rhi = own ? rc : f.rhi;
+      dh = own ? root : dh;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_for<0, N>(column);
+  if (!__all(range < kSpan)) {     // also a pivot that is negative or not finite
+    wsync();
+    chol_any<LDN, N, R>(A, ok);
+    f.template load<LDN>(A);
+    wsync();
+    return;
+  }
+  f.dlo = dl;
+  f.dhi = dh;
+  if (store) {
+    // 16 lanes store the first rows, the next 16 the others
+    if ((ln & 15) < H && ln < 32) {
+      const bool first = ln < 16;
+      const R diag = first ? dl : dh;
+      R* o = A + (first ? rl : rl + H) * L;
+      PKS_UNROLL for (int k = 0; k < H; ++k) o[k] = first ? (k < rl ? f.lo[k] : R(0)) : f.hi[k];
+      PKS_UNROLL for (int k = H; k < N; ++k) o[k] = first || k - H >= rl ? R(0) : f.hi[k];
+      o[first ? rl : rl + H] = diag;
+    }
   }
   wsync();
 }
 
-// B <- Lc^-T B (back substitution).
-template <int LDN, int N, int NC, typename R>
-PKS_DEV void bwd(const R* Lc, R* B) {
-  constexpr int L = ld<LDN>();
-  for (int c = lane(); c < NC; c += kWave) {
-    R x[N];
-    PKS_UNROLL for (int i = 0; i < N; ++i) x[i] = B[i * L + c];
-    PKS_UNROLL for (int i = N - 1; i >= 0; --i) {
-      R s = x[i];
-      PKS_UNROLL for (int t = i + 1; t < N; ++t) s = fma(-Lc[t * L + i], x[t], s);
-      x[i] = s / Lc[i * L + i];
+template <int LDN, int N, typename R>
+PKS_DEV void chol(R* A, int* ok) {
+  Factor<N, R> f;
+  chol<LDN, N>(A, ok, f, true);
+}
+
+// x <- Lc^-1 x and x <- Lc^-T x for one vector per lane, in registers; the
+// sums run in the order of the rows they come from (ascending).  An FP64
+// multiply-add issues every 4 cycles and its result is ready after 5, so the
+// chains cost no more than their instructions.
+template <int N>
+PKS_DEV void quotient(const Factor<N, double>&, double& x, double d, double r) {
+  const double q = x * r;                      // Markstein's correction: rounded as a division
+  x = fma(fma(-q, d, x), r, q);
+}
+template <int N>
+PKS_DEV void quotient(const Factor<N, float>&, float& x, float, double r) { x = float(double(x) * r); }
+
+template <int N, typename R>
+PKS_DEV void solve_l(const Factor<N, R>& f, R (&x)[N]) {
+  constexpr int H = N / 2;
+  static_for<0, N>([&](auto T) {
+    constexpr int t = decltype(T)::value, n = t + 1;
+    quotient(f, x[t], f.template diag<t>(), f.template rcp<t>());
+    if constexpr (n < H) fnma_lanes<n % H, n < H ? H - n : 0>(x + n, f.lo[n < H ? t : 0], x[t]);
+    constexpr int m = n > H ? n : H;   // rows of the upper half
+    if constexpr (m < N) fnma_lanes<m % H, N - m>(x + m, f.hi[t], x[t]);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+template <int N, typename R>
+PKS_DEV void solve_lt(const Factor<N, R>& f, R (&x)[N]) {
+  constexpr int H = N / 2;
+  static_for<0, N>([&](auto V) {
+    constexpr int i = N - 1 - decltype(V)::value, n = i + 1;
+    if constexpr (n < H) fnma_sum<n % H, n < H ? H - n : 0>(x[i], f.lo[n < H ? i : 0], x + n);
+    constexpr int m = n > H ? n : H;
+    if constexpr (m < N) fnma_sum<m % H, N - m>(x[i], f.hi[i], x + m);
+    quotient(f, x[i], f.template diag<i>(), f.template rcp<i>());
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+// A vector of N words in LDS per lane: entry i at p[i * st]; lanes without one
+// read some other lane's and store nothing.
+template <typename R>
+struct Vec {
+  R* p;
+  int st;
+  bool live;
+  template <int N>
+  PKS_DEV void get(R (&x)[N]) const { PKS_UNROLL for (int i = 0; i < N; ++i) x[i] = p[i * st]; }
+  template <int N>
+  PKS_DEV void put(const R (&x)[N]) const {
+    if (live) {
+      PKS_UNROLL for (int i = 0; i < N; ++i) p[i * st] = x[i];
     }
-    PKS_UNROLL for (int i = 0; i < N; ++i) B[i * L + c] = x[i];
   }
+};
+// Columns 0 .. NC - 1 of B for the lanes from `first` on, as lane ln sees it.
+template <int LDN, int NC, typename R>
+PKS_DEV Vec<R> columns(int ln, R* B, int first = 0) {
+  const int c = ln - first;
+  const bool live = c >= 0 && c < NC;
+  return Vec<R>{B + (live ? c : 0), ld<LDN>(), live};
+}
+
+// B <- L^-1 B, B N x NC, and x <- L^-1 x of one vector (null: none) beside it.
+template <int LDN, int NC, int N, typename R>
+PKS_DEV void fwd(const Factor<N, R>& f, R* B, R* x = nullptr) {
+  static_assert(NC < kWave, "a lane per column, one for the vector");
+  const int ln = lane();
+  Vec<R> v = columns<LDN, NC>(ln, B);
+  if (x && ln == NC) v = Vec<R>{x, 1, true};
+  R c[N];
+  v.get(c);
+  solve_l(f, c);
+  v.put(c);
   wsync();
 }
 
-// x <- Lc^-1 x for one vector (lane 0, in registers).
+// The same for two matrices and a vector.
+template <int LDN, int NC, int N, typename R>
+PKS_DEV void fwd2(const Factor<N, R>& f, R* B1, R* B2, R* x) {
+  static_assert(2 * NC < kWave, "a lane per column, one for the vector");
+  const int ln = lane();
+  Vec<R> v = ln < NC ? columns<LDN, NC>(ln, B1) : columns<LDN, NC>(ln, B2, NC);
+  if (ln == 2 * NC) v = Vec<R>{x, 1, true};
+  R c[N];
+  v.get(c);
+  solve_l(f, c);
+  v.put(c);
+  wsync();
+}
+
+// B <- L^-1 U^T, U N x N.
+template <int LDN, int N, typename R>
+PKS_DEV void fwd_t(const Factor<N, R>& f, const R* U, R* B) {
+  const int ln = lane();
+  const Vec<R> v = columns<LDN, N>(ln, B);
+  const R* u = U + (v.live ? ln : 0) * ld<LDN>();
+  R c[N];
+  PKS_UNROLL for (int i = 0; i < N; ++i) c[i] = u[i];
+  solve_l(f, c);
+  v.put(c);
+  wsync();
+}
+
+// x <- Lc^-1 x for one vector, Lc in LDS.
 template <int LDN, int N, typename R>
 PKS_DEV void fwd_vec(const R* Lc, R* x) {
-  constexpr int L = ld<LDN>();
-  if (lane() == 0) {
-    R y[N];
-    PKS_UNROLL for (int i = 0; i < N; ++i) y[i] = x[i];
-    PKS_UNROLL for (int i = 0; i < N; ++i) {
-      R s = y[i];
-      PKS_UNROLL for (int t = 0; t < i; ++t) s = fma(-Lc[i * L + t], y[t], s);
-      y[i] = s / Lc[i * L + i];
-    }
-    PKS_UNROLL for (int i = 0; i < N; ++i) x[i] = y[i];
-  }
+  Factor<N, R> f;
+  f.template load<LDN>(Lc);
+  const Vec<R> v{x, 1, lane() == 0};
+  R c[N];
+  v.get(c);
+  wsync();
+  solve_l(f, c);
+  v.put(c);
   wsync();
 }
+
+// B <- Lc^-T B (back substitution), Lc in LDS; lane per column.
+template <int LDN, int N, int NC, typename R>
+PKS_DEV void bwd(const R* Lc, R* B) {
+  static_assert(NC <= kWave, "a lane per column");
+  Factor<N, R> f;
+  f.template load<LDN>(Lc);
+  const Vec<R> v = columns<LDN, NC>(lane(), B);
+  R c[N];
+  v.get(c);
+  solve_lt(f, c);
+  v.put(c);
+  wsync();
+}
+
+// Lane mapping of the element-by-element routines: the lanes take whole rows
+// of NC entries, kWave / NC rows per pass, so that a lane's entries are a
+// constant number of rows apart (one address, immediate offsets, no division
+// per entry).  f(pass, i, j) runs with row i = first row + pass * rows.
+template <int M, int NC>
+struct Rows {
+  static constexpr int per = kWave / NC;             // rows per pass
+  static constexpr int passes = (M + per - 1) / per;
+  int i0, j;
+  PKS_DEV Rows() {
+    const int l = lane();
+    i0 = l / NC;
+    j = l - i0 * NC;
+  }
+  // whether this lane has an entry in pass r
+  PKS_DEV bool live(int r) const { return i0 < per && (M % per == 0 || r + 1 < passes || i0 + r * per < M); }
+};
 
 // A <- (A + A^T) / 2
 template <int LDN, int N, typename R>
 PKS_DEV void symmetrize(R* A) {
-  // all reads issued before the first store (one LDS latency, not one per pass);
-  // each pair (i < j) belongs to one lane
+  // all reads issued before the first store (one LDS latency, not one per
+  // pass); both entries of a pair form the same sum
   constexpr int L = ld<LDN>();
-  constexpr int T = N * N, RN = (T + kWave - 1) / kWave;
-  R v[RN];
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / N, j = e - i * N;
-    v[r] = (e < T && j > i) ? R(0.5) * (A[i * L + j] + A[j * L + i]) : R(0);
+  using Rw = Rows<N, N>;
+  const Rw w;
+  const int i0 = w.i0 < Rw::per ? w.i0 : 0;
+  const R *a = A + i0 * L + w.j, *at = A + w.j * L + i0;
+  R v[Rw::passes];
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r) {
+    const int q = w.live(r) ? r : 0;
+    v[r] = R(0.5) * (a[q * Rw::per * L] + at[q * Rw::per]);
   }
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / N, j = e - i * N;
-    if (e < T && j > i) {
-      A[i * L + j] = v[r];
-      A[j * L + i] = v[r];
-    }
-  }
+  R* o = A + i0 * L + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) o[r * Rw::per * L] = v[r];
   wsync();
 }
 
@@ -251,25 +647,42 @@ template <int LDN, int M, int NC, bool TR, typename R>
 PKS_DEV void copy(const R* A, R* B) {   // B = op(A), M x NC
   // all reads issued before the first store, as in symmetrize
   constexpr int L = ld<LDN>();
-  constexpr int T = M * NC, RN = (T + kWave - 1) / kWave;
-  R v[RN];
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / NC, j = e - i * NC;
-    v[r] = e < T ? (TR ? A[j * L + i] : A[i * L + j]) : R(0);
-  }
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / NC, j = e - i * NC;
-    if (e < T) B[i * L + j] = v[r];
-  }
+  using Rw = Rows<M, NC>;
+  const Rw w;
+  const int i0 = w.i0 < Rw::per ? w.i0 : 0;
+  const R* a = TR ? A + w.j * L + i0 : A + i0 * L + w.j;
+  constexpr int step = TR ? Rw::per : Rw::per * L;
+  R v[Rw::passes];
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r) v[r] = a[(w.live(r) ? r : 0) * step];
+  R* o = B + i0 * L + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) o[r * Rw::per * L] = v[r];
   wsync();
 }
 
 template <int LDN, int M, int NC, typename R>
 PKS_DEV void zero(R* A) {
-  constexpr int L = ld<LDN>();
-  for (int e = lane(); e < M * NC; e += kWave) A[(e / NC) * L + e % NC] = R(0);
+  using Rw = Rows<M, NC>;
+  const Rw w;
+  R* o = A + w.i0 * ld<LDN>() + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) o[r * Rw::per * ld<LDN>()] = R(0);
+  wsync();
+}
+
+// B <- A - B
+template <int LDN, int M, int NC, typename R>
+PKS_DEV void rsub(const R* A, R* B) {
+  using Rw = Rows<M, NC>;
+  const Rw w;
+  const int o = (w.i0 < Rw::per ? w.i0 : 0) * ld<LDN>() + w.j;
+  R v[Rw::passes];
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r) {
+    const int q = (w.live(r) ? r : 0) * Rw::per * ld<LDN>();
+    v[r] = A[o + q] - B[o + q];
+  }
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) B[o + r * Rw::per * ld<LDN>()] = v[r];
   wsync();
 }
 
@@ -282,64 +695,55 @@ PKS_DEV void vcopy(const R* x, R* y) {
 // --- HBM <-> LDS ------------------------------------------------------------
 // The element type in HBM (RG) may differ from the one in LDS (R): the FP32
 // engine's linearisation works in FP64 on its FP32 records.
-template <int LDN, int M, int NC, typename RG, typename R>
-PKS_DEV void ld_full(const RG* g, R* A) {
-  // all global loads are issued before the first LDS store (fixed trip
-  // counts), so one record costs one memory latency, not one per pass
-  constexpr int L = ld<LDN>();
-  constexpr int T = M * NC, RN = (T + kWave - 1) / kWave;
-  R v[RN];
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    v[r] = e < T ? R(g[e]) : R(0);
-  }
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    if (e < T) A[(e / NC) * L + e % NC] = v[r];
-  }
+// All global loads are issued before the first LDS store, so one record costs
+// one memory latency, not one per pass.
+template <int LDN, int M, int NC, bool ADD, typename RG, typename R>
+PKS_DEV void ld_rows(const RG* g, R* A) {
+  using Rw = Rows<M, NC>;
+  const Rw w;
+  const RG* p = g + (w.i0 < Rw::per ? w.i0 : 0) * NC + w.j;
+  R v[Rw::passes];
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r) v[r] = R(p[(w.live(r) ? r : 0) * Rw::per * NC]);
+  R* o = A + w.i0 * ld<LDN>() + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) {
+      R& x = o[r * Rw::per * ld<LDN>()];
+      x = ADD ? x + v[r] : v[r];
+    }
 }
-// A += g (row-major M x NC in HBM), loads issued first as in ld_full
 template <int LDN, int M, int NC, typename RG, typename R>
-PKS_DEV void add_full(const RG* g, R* A) {
-  constexpr int L = ld<LDN>();
-  constexpr int T = M * NC, RN = (T + kWave - 1) / kWave;
-  R v[RN];
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    v[r] = e < T ? R(g[e]) : R(0);
-  }
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    if (e < T) A[(e / NC) * L + e % NC] += v[r];
-  }
-}
+PKS_DEV void ld_full(const RG* g, R* A) { ld_rows<LDN, M, NC, false>(g, A); }
+// A += g (row-major M x NC in HBM)
+template <int LDN, int M, int NC, typename RG, typename R>
+PKS_DEV void add_full(const RG* g, R* A) { ld_rows<LDN, M, NC, true>(g, A); }
 template <int LDN, int M, int NC, typename R, typename RG>
 PKS_DEV void st_full(const R* A, RG* g) {
-  constexpr int L = ld<LDN>();
-  for (int e = lane(); e < M * NC; e += kWave) g[e] = RG(A[(e / NC) * L + e % NC]);
+  using Rw = Rows<M, NC>;
+  const Rw w;
+  const R* a = A + w.i0 * ld<LDN>() + w.j;
+  RG* p = g + w.i0 * NC + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) p[r * Rw::per * NC] = RG(a[r * Rw::per * ld<LDN>()]);
 }
 template <int LDN, int N, typename RG, typename R>
 PKS_DEV void ld_symm(const RG* g, R* A) {
-  constexpr int L = ld<LDN>();
-  constexpr int T = N * N, RN = (T + kWave - 1) / kWave;
-  R v[RN];
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / N, j = e - i * N;
-    v[r] = e < T ? R(g[sym_index<N>(i, j)]) : R(0);
-  }
-  PKS_UNROLL for (int r = 0; r < RN; ++r) {
-    const int e = r * kWave + lane();
-    const int i = e / N, j = e - i * N;
-    if (e < T) A[i * L + j] = v[r];
-  }
+  using Rw = Rows<N, N>;
+  const Rw w;
+  R v[Rw::passes];
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    v[r] = R(g[w.live(r) ? sym_index<N>(w.i0 + r * Rw::per, w.j) : 0]);
+  R* o = A + w.i0 * ld<LDN>() + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r)
+    if (w.live(r)) o[r * Rw::per * ld<LDN>()] = v[r];
 }
 template <int LDN, int N, typename R, typename RG>
 PKS_DEV void st_symm(const R* A, RG* g) {
-  constexpr int L = ld<LDN>();
-  for (int e = lane(); e < N * N; e += kWave) {
-    const int i = e / N, j = e - i * N;
-    if (j >= i) g[sym_index<N>(i, j)] = RG(A[i * L + j]);
+  using Rw = Rows<N, N>;
+  const Rw w;
+  const R* a = A + w.i0 * ld<LDN>() + w.j;
+  PKS_UNROLL for (int r = 0; r < Rw::passes; ++r) {
+    const int i = w.i0 + r * Rw::per;
+    if (w.live(r) && w.j >= i) g[sym_index<N>(i, w.j)] = RG(a[r * Rw::per * ld<LDN>()]);
   }
 }
 template <int N, typename RG, typename R>
@@ -404,6 +808,31 @@ PKS_DEV void take_restart(const R* rA, const R* rb, const R* rC, R* lA, R* lb, R
   wsync();
 }
 
+// S = I + U^T J U (S may be J) and v = e - J b; T is scratch.
+template <int N, typename R>
+PKS_DEV void gain_matrix(const R* U, const R* b, const R* e, const R* J, R* S, R* T, R* v) {
+  constexpr const R* none = nullptr;
+  mm<N, N, N, N, false, false>(J, U, none, R(1), T, b, e, R(-1), v);   // J U
+  mm<N, N, N, N, true, false>(U, T, none, R(1), S);
+  for (int i = lane(); i < N; i += kWave) S[i * ld<N>() + i] += R(1);
+  wsync();
+}
+
+// C = U U^T (in place: C becomes U), G = I + U^T J U (in S, which may be J) =
+// Lg Lg^T and W = Lg^-1 U^T (in T); v = e - J b.  One copy of the
+// factorisation serves both matrices: it is straight-line code of 9 KB, and
+// two CUs share 64 KB of instruction cache.
+template <int N, typename R>
+PKS_DEV void gain_factors(R* C, const R* b, const R* e, const R* J, R* S, R* T, R* v, int* ok) {
+  Factor<N, R> f;
+#pragma unroll 1
+  for (int ph = 0; ph < 2; ++ph) {
+    if (ph == 1) gain_matrix<N>(C, b, e, J, S, T, v);
+    chol<N, N>(ph == 0 ? C : S, ok, f, ph == 0);
+  }
+  fwd_t<N>(f, C, T);
+}
+
 // --- the filtering operator (eq. 15), symmetric pivot-free form ------------
 // l <- l (x) r with l = (lA, lb, lC, le, lJ), r = (rA, rb, C_j, re, rJ).  Same
 // algebra as FilterOp::combine.  l's C holds its Cholesky factor and then M
@@ -413,40 +842,25 @@ PKS_DEV void take_restart(const R* rA, const R* rb, const R* rC, R* lA, R* lb, R
 template <int N, typename R, class GetC>
 PKS_DEV void combine_f_impl(R* lA, R* lb, R* lC, R* le, R* lJ, const R* rA, const R* rb, const R* re, R* rJ, R* S,
                             R* T, R* v1, R* v2, int* ok, GetC getC) {
-  mv<N, N, N, false>(rJ, lb, re, R(-1), v1);            // v = eta_j - J b_i
-  chol<N, N>(lC, ok);                                   // U
-  mm<N, N, N, N, false, false>(rJ, lC, (const R*)nullptr, R(1), T);      // J U
-  mm<N, N, N, N, true, false>(lC, T, (const R*)nullptr, R(1), S);        // U^T J U
-  for (int i = lane(); i < N; i += kWave) S[i * ld<N>() + i] += R(1);   // G
-  wsync();
-  chol<N, N>(S, ok);                                    // Lg
-  copy<N, N, N, true>(lC, T);                           // U^T
-  fwd<N, N, N>(S, T);                                   // W = Lg^-1 U^T
+  constexpr const R* none = nullptr;
+  gain_factors<N>(lC, lb, re, rJ, S, T, v1, ok);         // lC = U, T = W, v1 = v
   mm<N, N, N, N, true, false>(T, T, (const R*)nullptr, R(1), lC);        // M = W^T W
   mm<N, N, N, N, false, false>(rJ, lA, (const R*)nullptr, R(1), S);      // Y = J A_i
-  mm<N, N, N, N, false, false>(lC, S, (const R*)nullptr, R(1), T);       // Z = M Y
-  mv<N, N, N, false>(lC, v1, (const R*)nullptr, R(1), v2);               // u = M v
+  mm<N, N, N, N, false, false>(lC, S, none, R(1), T, v1, none, R(1), v2);  // Z = M Y; u = M v
   // J_ij = A_i^T Y - Y^T Z + J_i ; eta_ij = A_i^T v - Y^T u + eta_i
-  mm<N, N, N, N, true, false>(lA, S, lJ, R(1), lJ);
-  mm<N, N, N, N, true, false>(S, T, lJ, R(-1), lJ);
-  mv<N, N, N, true>(lA, v1, le, R(1), le);
-  mv<N, N, N, true>(S, v2, le, R(-1), le);
+  mm<N, N, N, N, true, false>(lA, S, lJ, R(1), lJ, v1, le, R(1), le);
+  mm<N, N, N, N, true, false>(S, T, lJ, R(-1), lJ, v2, le, R(-1), le);
   symmetrize<N, N>(lJ);
   // b_ij = A_j (b_i + u) + b_j
   for (int i = lane(); i < N; i += kWave) v1[i] = lb[i] + v2[i];
   wsync();
-  mv<N, N, N, false>(rA, v1, rb, R(1), lb);
   // C_ij = A_j M A_j^T + C_j
-  mm<N, N, N, N, false, false>(rA, lC, (const R*)nullptr, R(1), rJ);     // A_j M
+  mm<N, N, N, N, false, false>(rA, lC, none, R(1), rJ, v1, rb, R(1), lb);  // A_j M
   const R* rC = getC(S);
   mm<N, N, N, N, false, true>(rJ, rA, rC, R(1), lC);
   symmetrize<N, N>(lC);
   // A_ij = A_j (A_i - Z)
-  for (int e = lane(); e < N * N; e += kWave) {
-    const int i = e / N, j = e - i * N;
-    T[i * ld<N>() + j] = lA[i * ld<N>() + j] - T[i * ld<N>() + j];
-  }
-  wsync();
+  rsub<N, N, N>(lA, T);
   mm<N, N, N, N, false, false>(rA, T, (const R*)nullptr, R(1), lA);
   if (!(lb[0] == lb[0]) && all_zero<N>(rA)) take_restart<N>(rA, rb, rC, lA, lb, lC);
 }
@@ -473,6 +887,21 @@ PKS_DEV void combine_f_lean(R* lA, R* lb, R* lC, R* le, R* lJ, const R* rA, cons
   });
 }
 
+// The carry application after gain_factors: from T = W and v1 = v.
+template <int N, typename R, class GetC>
+PKS_DEV void apply_gain(R* cb, R* cC, const R* rA, const R* rb, R* rJ, R* T, R* v1, R* v2, GetC getC) {
+  constexpr const R* none = nullptr;
+  mm<N, N, N, N, true, false>(T, T, (const R*)nullptr, R(1), cC);        // M = W^T W
+  mv<N, N, N, false>(cC, v1, (const R*)nullptr, R(1), v2);               // u = M v
+  for (int i = lane(); i < N; i += kWave) v1[i] = cb[i] + v2[i];
+  wsync();
+  mm<N, N, N, N, false, false>(rA, cC, none, R(1), T, v1, rb, R(1), cb);   // A M
+  const R* rC = getC(rJ);
+  mm<N, N, N, N, false, true>(T, rA, rC, R(1), cC);     // A M A^T + C
+  symmetrize<N, N>(cC);
+  if (!(cb[0] == cb[0]) && all_zero<N>(rA)) take_restart<N>(rA, rb, rC, (R*)nullptr, cb, cC);
+}
+
 // Carry (b, C) (x) r: the filtered mean and covariance after element r.  The
 // carry's covariance holds its Cholesky factor and then M while the result is
 // formed, rJ holds G and its factor (rJ is destroyed), T is scratch.  The
@@ -481,25 +910,8 @@ PKS_DEV void combine_f_lean(R* lA, R* lb, R* lC, R* le, R* lJ, const R* rA, cons
 template <int N, typename R, class GetC>
 PKS_DEV void apply_f_impl(R* cb, R* cC, const R* rA, const R* rb, const R* re, R* rJ, R* T, R* v1, R* v2, int* ok,
                           GetC getC) {
-  mv<N, N, N, false>(rJ, cb, re, R(-1), v1);            // v = eta - J b, before rJ is reused
-  chol<N, N>(cC, ok);                                   // U
-  mm<N, N, N, N, false, false>(rJ, cC, (const R*)nullptr, R(1), T);      // J U
-  mm<N, N, N, N, true, false>(cC, T, (const R*)nullptr, R(1), rJ);       // U^T J U
-  for (int i = lane(); i < N; i += kWave) rJ[i * ld<N>() + i] += R(1);  // G
-  wsync();
-  chol<N, N>(rJ, ok);                                   // Lg
-  copy<N, N, N, true>(cC, T);                           // U^T
-  fwd<N, N, N>(rJ, T);                                  // W = Lg^-1 U^T
-  mm<N, N, N, N, true, false>(T, T, (const R*)nullptr, R(1), cC);        // M = W^T W
-  mv<N, N, N, false>(cC, v1, (const R*)nullptr, R(1), v2);               // u = M v
-  for (int i = lane(); i < N; i += kWave) v1[i] = cb[i] + v2[i];
-  wsync();
-  mv<N, N, N, false>(rA, v1, rb, R(1), cb);
-  mm<N, N, N, N, false, false>(rA, cC, (const R*)nullptr, R(1), T);      // A M
-  const R* rC = getC(rJ);
-  mm<N, N, N, N, false, true>(T, rA, rC, R(1), cC);     // A M A^T + C
-  symmetrize<N, N>(cC);
-  if (!(cb[0] == cb[0]) && all_zero<N>(rA)) take_restart<N>(rA, rb, rC, (R*)nullptr, cb, cC);
+  gain_factors<N>(cC, cb, re, rJ, rJ, T, v1, ok);        // cC = U, T = W, v1 = v
+  apply_gain<N, R>(cb, cC, rA, rb, rJ, T, v1, v2, getC);
 }
 
 // All operands in LDS; one scratch matrix T, rJ destroyed.
@@ -530,10 +942,10 @@ PKS_DEV void combine_s(R* lE, R* lg, R* lL, const R* rE, const R* rg, const R* r
   // E_l = 0 (a track's end element or an aggregate holding one): the result
   // is l itself; l is updated in place, so the restart is taken up front.
   if (lE[0] == R(0) && all_zero<N>(lE)) return;
-  mm<N, N, N, N, false, false>(lE, rL, (const R*)nullptr, R(1), T1);
+  constexpr const R* none = nullptr;
+  mm<N, N, N, N, false, false>(lE, rL, none, R(1), T1, rg, none, R(1), v1);
   mm<N, N, N, N, false, true>(T1, lE, lL, R(1), lL);
   symmetrize<N, N>(lL);
-  mv<N, N, N, false>(lE, rg, (const R*)nullptr, R(1), v1);
   mm<N, N, N, N, false, false>(lE, rE, (const R*)nullptr, R(1), T2);
   copy<N, N, N, false>(T2, lE);
   for (int i = lane(); i < N; i += kWave) lg[i] += v1[i];
@@ -543,10 +955,9 @@ PKS_DEV void combine_s(R* lE, R* lg, R* lL, const R* rE, const R* rg, const R* r
 // r (x) carry (g, L): the smoothed mean and covariance before the carry.
 template <int N, typename R>
 PKS_DEV void apply_s(const R* rE, const R* rg, const R* rL, R* cg, R* cL, R* T1, R* v1) {
-  mm<N, N, N, N, false, false>(rE, cL, (const R*)nullptr, R(1), T1);
+  mm<N, N, N, N, false, false>(rE, cL, (const R*)nullptr, R(1), T1, cg, rg, R(1), v1);
   mm<N, N, N, N, false, true>(T1, rE, rL, R(1), cL);
   symmetrize<N, N>(cL);
-  mv<N, N, N, false>(rE, cg, rg, R(1), v1);
   vcopy<N>(v1, cg);
   if (!(cg[0] == cg[0] && cL[0] == cL[0]) && all_zero<N>(rE)) take_restart<N>(rE, rg, rL, (R*)nullptr, cg, cL);
 }
@@ -567,14 +978,14 @@ PKS_DEV void slr(int lin, SigmaRule rule, const R* xbar, R* Pbar, Eval eval, R* 
   sigma_weights<N, R>(lin, rule, gamma, w0, wj);
   // all 2N + 1 points in one pass: lane 2N takes the centre
   static_assert(2 * N + 1 <= kWave, "one sigma point per lane");
-  if (lane() <= 2 * N) {
-    const bool centre = lane() == 2 * N;
-    const int j = lane() < N ? lane() : (centre ? 0 : lane() - N);
-    const R sg = lane() < N ? gamma : -gamma;
+  if (const int ln = lane(); ln <= 2 * N) {
+    const bool centre = ln == 2 * N;
+    const int j = ln < N ? ln : (centre ? 0 : ln - N);
+    const R sg = ln < N ? gamma : -gamma;
     R x[N], z[Q];
     PKS_UNROLL for (int i = 0; i < N; ++i) x[i] = centre ? xbar[i] : xbar[i] + sg * Pbar[i * L + j];
     eval(x, z);
-    R* out = centre ? zc : (lane() < N ? Zp + j * L : Zm + j * L);
+    R* out = centre ? zc : (ln < N ? Zp + j * L : Zm + j * L);
     PKS_UNROLL for (int q = 0; q < Q; ++q) out[q] = z[q];
   }
   wsync();
@@ -725,20 +1136,19 @@ struct Dense {
     R* HQ = T;          // P x N
     R* HF = T + P * L;  // P x N
     mm<N, P, N, N, false, false>(H, Qp, (const R*)nullptr, R(1), HQ);
-    mm<N, P, N, N, false, false>(H, F, (const R*)nullptr, R(1), HF);
+    mm<N, P, N, N, false, false>(H, F, (const R*)nullptr, R(1), HF, c, yt, R(-1), yt);   // w = y - H c - d
     mm<N, P, N, P, false, true>(HQ, H, Sx, R(1), Sx);                      // S = H Q' H^T + R'
-    chol<N, P>(Sx, &w.ok);
-    mv<N, P, N, false>(H, c, yt, R(-1), yt);                                // w = y - H c - d
     for (int i = lane(); i < P; i += kWave) yt[i] -= d[i];
     wsync();
-    fwd<N, P, N>(Sx, HQ);                                                   // Zs = Ls^-1 H Q'
-    fwd<N, P, N>(Sx, HF);                                                   // Ys = Ls^-1 H F
-    fwd_vec<N, P>(Sx, yt);                                                  // ws = Ls^-1 w
-    mv<N, N, P, true>(HQ, yt, c, R(1), b);                                  // b = c + Zs^T ws
-    mv<N, N, P, true>(HF, yt, (const R*)nullptr, R(1), e);                  // eta = Ys^T ws
-    mm<N, N, P, N, true, false>(HQ, HF, F, R(-1), A);                       // A = F - Zs^T Ys
+    {
+      Factor<P, R> Ls;
+      chol<N, P>(Sx, &w.ok, Ls, false);
+      fwd2<N, N>(Ls, HQ, HF, yt);                     // Zs = Ls^-1 H Q', Ys = Ls^-1 H F, ws = Ls^-1 w
+    }
+    mm<N, N, P, N, true, false>(HQ, HF, F, R(-1), A, yt, c, R(1), b);       // A = F - Zs^T Ys, b = c + Zs^T ws
     mm<N, N, P, N, true, false>(HQ, HQ, Qp, R(-1), C);                      // C = Q' - Zs^T Zs
-    mm<N, N, P, N, true, false>(HF, HF, (const R*)nullptr, R(1), J);       // J = Ys^T Ys
+    mm<N, N, P, N, true, false>(HF, HF, (const R*)nullptr, R(1), J, yt, (const R*)nullptr, R(1), e);
+                                                                            // J = Ys^T Ys, eta = Ys^T ws
     symmetrize<N, N>(C);
     symmetrize<N, N>(J);
     if constexpr (WT::kNM >= 9) {
@@ -770,10 +1180,11 @@ struct Dense {
     }
     for (int i = lane(); i < N; i += kWave) v[i] = xbar[i] - b[i];
     wsync();
-    chol<N, N>(G, &w.ok);
-    fwd<N, N, N>(G, Z);
-    fwd<N, N, N>(G, V);
-    fwd_vec<N, N>(G, v);
+    {
+      Factor<N, R> Lg;
+      chol<N, N>(G, &w.ok, Lg, false);
+      fwd2<N, N>(Lg, Z, V, v);
+    }
     mv<N, N, N, true>(Z, v, b, lam, b);
     mv<N, N, N, true>(V, v, e, lam, e);
     mm<N, N, N, N, true, false>(Z, V, A, -lam, A);
@@ -1034,41 +1445,67 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(sizeof(R)
     ld_v<N>(rec + N * N + N + Lay::kS, re);
     ld_symm<N, N>(rec + N * N + 2 * N + Lay::kS, rJ);
     wsync();
-    if (have) {
-      apply_f_lean<N, R>(cx, cP, rA, rb, recC, re, rJ, T, w.v[2], w.v[3], &w.ok);
-    } else {
+    const bool last = a.flags[s] & kSlotLast;
+    if (!have) {
       vcopy<N>(rb, cx);
       ld_symm<N, N>(recC, cP);
       wsync();
     }
-    have = true;
-    // smoothing element of slot s into (eE, eg, eL) = (m[0], rb, m[1]): the
-    // filtering element is spent
+    // The carry application (the steps of gain_factors and apply_gain), then
+    // the smoothing element of slot s into (eE, eg, eL) = (m[0], rb, m[1]),
+    // the filtering element being spent.  Phases 0, 1 and 2 factorise P*, G
+    // and P^-; one copy of the factorisation and of the substitution serves
+    // them (see gain_factors).
     R *eE = w.m[0], *eg = rb, *eL = w.m[1];
-    if (a.flags[s] & kSlotLast) {
+    R *F = w.m[1], *Pp = w.m[0], *V = T, *v = w.v[2], *t = w.v[3];
+#pragma unroll 1
+    for (int ph = have ? 0 : 2; ph < (last ? 2 : 3); ++ph) {
+      if (ph == 1) {
+        gain_matrix<N>(cP, cx, re, rJ, rJ, T, v);
+      } else if (ph == 2) {
+        const R* tr = static_cast<const R*>(a.trans) + size_t(s) * Lay::kTrans;
+        ld_full<N, N, N>(tr, F);
+        ld_symm<N, N>(tr + N * N + N, Pp);
+        ld_v<N>(tr + N * N, v);
+        wsync();
+        mm<N, N, N, N, false, false>(F, cP, (const R*)nullptr, R(1), V, cx, v, R(1), t);   // F P*, F x* + c
+        mm<N, N, N, N, false, true>(V, F, Pp, R(1), Pp);                  // F P* F^T + Q'
+        symmetrize<N, N>(Pp);
+      }
+      Factor<N, R> f;
+      chol<N, N>(ph == 0 ? cP : (ph == 1 ? rJ : Pp), &w.ok, f, ph == 0);
+      if (ph == 0) continue;
+      // W = Lg^-1 U^T into T; V = Lp^-1 F P* in place, t <- Lp^-1 (F x* + c)
+      const int ln = lane(), row = (ln < N ? ln : 0) * L;
+      Vec<R> d = columns<N, N>(ln, T);
+      if (ph == 2 && ln == N) d = Vec<R>{t, 1, true};
+      const Vec<R> src = ph == 1 ? Vec<R>{cP + row, 1, false} : d;
+      R x[N];
+      src.get(x);
+      solve_l(f, x);
+      d.put(x);
+      if (ph == 1) {
+        wsync();
+        apply_gain<N, R>(cx, cP, rA, rb, rJ, T, v, t, [&](R* buf) {
+          ld_symm<N, N>(recC, buf);
+          wsync();
+          return static_cast<const R*>(buf);
+        });
+      } else {
+        // E^T = Lp^-T V, stored transposed over P^-
+        solve_lt(f, x);
+        Vec<R>{eE + row, 1, ln < N}.put(x);
+        wsync();
+        // L_s = P* - V^T V, g = x* - V^T Lp^-1 (F x* + c)
+        mm<N, N, N, N, true, false>(V, V, cP, R(-1), eL, t, cx, R(-1), eg);
+        symmetrize<N, N>(eL);
+      }
+    }
+    have = true;
+    if (last) {
       zero<N, N, N>(eE);
       vcopy<N>(cx, eg);
       copy<N, N, N, false>(cP, eL);
-    } else {
-      const R* tr = static_cast<const R*>(a.trans) + size_t(s) * Lay::kTrans;
-      R *F = w.m[1], *FP = w.m[2], *Pp = w.m[0], *V = w.m[2];
-      R *r = w.v[2], *t = w.v[3];
-      ld_full<N, N, N>(tr, F);
-      ld_symm<N, N>(tr + N * N + N, Pp);
-      ld_v<N>(tr + N * N, r);
-      wsync();
-      mm<N, N, N, N, false, false>(F, cP, (const R*)nullptr, R(1), FP);   // F P*
-      mm<N, N, N, N, false, true>(FP, F, Pp, R(1), Pp);                  // F P* F^T + Q'
-      symmetrize<N, N>(Pp);
-      mv<N, N, N, false>(F, cx, r, R(1), t);                              // F x* + c
-      chol<N, N>(Pp, &w.ok);
-      fwd<N, N, N>(Pp, V);                                                // V = Lp^-1 F P*
-      fwd_vec<N, N>(Pp, t);
-      mm<N, N, N, N, true, false>(V, V, cP, R(-1), eL);                   // L_s = P* - V^T V
-      symmetrize<N, N>(eL);
-      mv<N, N, N, true>(V, t, cx, R(-1), eg);                             // g = x* - V^T Lp^-1 (F x* + c)
-      bwd<N, N, N>(Pp, V);                                                // E^T = Lp^-T V
-      copy<N, N, N, true>(V, eE);
     }
     D::store_selem(eE, eg, eL, rec);
     if (s == s0) {

@@ -2,10 +2,9 @@
 // library, libdense_probe.so; nothing in libsmoother.so calls it).
 //
 // Products.  The engine multiplies 20 x 20 FP64 matrices held in LDS, one
-// wavefront per slot, with dn::mm: v_mfma_f64_16x16x4f64 on the product
-// padded to 32 x 32, 2 x 2 output tiles of 16 x 16, 5 steps of 4 along the
-// reduction, 20 MFMA per product (2.56 times the useful flops; MI355X's FP64
-// matrix peak equals its FP64 vector peak).  The alternative is the VALU
+// wavefront per slot, with dn::mm: v_mfma_f64_16x16x4f64 for 16 x 16 of the
+// result and v_mfma_f64_4x4x4f64 for its last four rows and columns (MI355X's
+// FP64 matrix peak equals its FP64 vector peak).  The alternative is the VALU
 // routine dn::mm_valu (each lane a 2 x 4 block of the result).  Both kernels
 // below take the engine's LDS layout and accumulate C = reps * A B, one
 // wavefront per block, so their durations compare the two forms directly.
@@ -20,6 +19,9 @@
 // eq. 15 combine, its carry application and the eq. 19 combine, on seeded
 // well-conditioned operands, with the shader clock (s_memtime) read by lane 0
 // around each call: per block, the sum over `reps` calls of each.
+//
+// Factors.  k_factor runs the engine's Cholesky factorisation and its forward
+// and back substitution on given matrices, for tests at the edges of its range.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -106,7 +108,9 @@ __global__ __launch_bounds__(64) void k_phases(unsigned long long* out, int reps
     PHASE(2, (pks::dn::mm<N, N, N, N, false, false>(rJ, T1, (const double*)nullptr, 1.0, T2)))
     PHASE(3, (pks::dn::mm<N, N, N, N, true, false>(T1, T2, (const double*)nullptr, 1.0, T3)))
     PHASE(4, (pks::dn::copy<N, N, N, true>(T1, T2)))
-    PHASE(5, (pks::dn::fwd<N, N, N>(T1, T2)))
+    pks::dn::Factor<N, double> f;
+    f.load<N>(T1);
+    PHASE(5, (pks::dn::fwd<N, N>(f, T2)))
     PHASE(6, (pks::dn::mv<N, N, N, false>(rJ, w.v[0], w.v[1], -1.0, w.v[4])))
     PHASE(7, (pks::dn::symmetrize<N, N>(lJ)))
     pks::dn::copy<N, N, N, false>(rJ, T3);   // the combine destroys its J operand
@@ -123,6 +127,40 @@ __global__ __launch_bounds__(64) void k_phases(unsigned long long* out, int reps
   }
   if (threadIdx.x == 0)
     for (int p = 0; p < kPhases; ++p) out[size_t(blockIdx.x) * kPhases + p] = acc[p];
+}
+
+// L L^T = A[b], X <- L^-1 X[b], Y <- L^-T L^-1 X[b] for n x n matrices, n = 20 or
+// 8; ok[b] = the factorisation's flag.
+template <int M, typename R>
+__global__ __launch_bounds__(64) void k_factor(const R* A, const R* X, R* Lo, R* Xo, R* Yo, int* ok) {
+  constexpr int LM = pks::dn::ld<M>();
+  __shared__ R a[M * LM], x[M * LM];
+  __shared__ int good;
+  const size_t off = size_t(blockIdx.x) * M * M;
+  for (int e = threadIdx.x; e < M * M; e += 64) {
+    a[(e / M) * LM + e % M] = A[off + e];
+    x[(e / M) * LM + e % M] = X[off + e];
+  }
+  if (threadIdx.x == 0) good = 1;
+  __syncthreads();
+  pks::dn::Factor<M, R> f;
+  pks::dn::chol<M, M>(a, &good, f, true);
+  pks::dn::fwd<M, M>(f, x);
+  for (int e = threadIdx.x; e < M * M; e += 64) {
+    Lo[off + e] = a[(e / M) * LM + e % M];
+    Xo[off + e] = x[(e / M) * LM + e % M];
+  }
+  __syncthreads();
+  pks::dn::bwd<M, M, M>(a, x);
+  for (int e = threadIdx.x; e < M * M; e += 64) Yo[off + e] = x[(e / M) * LM + e % M];
+  if (threadIdx.x == 0) ok[blockIdx.x] = good;
+}
+
+template <int M, typename R>
+int factor(int blocks, const void* A, const void* X, void* Lo, void* Xo, void* Yo, int* ok, hipStream_t s) {
+  hipLaunchKernelGGL((k_factor<M, R>), dim3(unsigned(blocks)), dim3(64), 0, s, static_cast<const R*>(A),
+                     static_cast<const R*>(X), static_cast<R*>(Lo), static_cast<R*>(Xo), static_cast<R*>(Yo), ok);
+  return int(hipGetLastError());
 }
 
 }  // namespace dprobe
@@ -142,6 +180,20 @@ int dprobe_products(int variant, int blocks, int reps, const double* A, const do
   else
     hipLaunchKernelGGL(dprobe::k_products_mfma, dim3(unsigned(blocks)), dim3(64), 0, s, A, B, C, reps);
   return int(hipGetLastError());
+}
+
+// The engine's factorisation and substitutions of `blocks` n x n matrices (n =
+// 20 or 8, FP64 or FP32 by `fp32`; device, row-major): L, L^-1 X and
+// L^-T L^-1 X, and the factorisation's flag per matrix.
+int dprobe_factor(int n, int fp32, int blocks, const void* A, const void* X, void* L, void* Xo, void* Yo, int* ok,
+                  void* stream) {
+  if (blocks < 1 || !A || !X || !L || !Xo || !Yo || !ok || (n != 20 && n != 8)) return int(hipErrorInvalidValue);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (n == 20)
+    return fp32 ? dprobe::factor<20, float>(blocks, A, X, L, Xo, Yo, ok, s)
+                : dprobe::factor<20, double>(blocks, A, X, L, Xo, Yo, ok, s);
+  return fp32 ? dprobe::factor<8, float>(blocks, A, X, L, Xo, Yo, ok, s)
+              : dprobe::factor<8, double>(blocks, A, X, L, Xo, Yo, ok, s);
 }
 
 // Number of routines k_phases times.

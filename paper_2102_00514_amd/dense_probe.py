@@ -5,7 +5,7 @@ by paper_2102_00514_amd.build).
     python -m paper_2102_00514_amd.dense_probe --phases [--blocks B] [--reps R]
 
 The first form compares the 20 x 20 x 20 FP64 products, the VALU routine
-against the engine's FP64 MFMA routine (v_mfma_f64_16x16x4f64), on the engine's
+against the engine's FP64 MFMA routine, on the engine's
 LDS layout: per variant the kernel time (HIP events, best of 5 launches) for B
 blocks (one wavefront each) of R chained products, the time per product and per
 wavefront, and the largest difference of the two results relative to the
@@ -32,6 +32,9 @@ def load():
     lib.dprobe_products.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p,
                                     ctypes.c_void_p, ctypes.c_void_p]
     lib.dprobe_products.restype = ctypes.c_int
+    vp, ci = ctypes.c_void_p, ctypes.c_int
+    lib.dprobe_factor.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp]
+    lib.dprobe_factor.restype = ci
     lib.dprobe_phase_count.argtypes = []
     lib.dprobe_phase_count.restype = ctypes.c_int
     lib.dprobe_phases.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
@@ -65,6 +68,21 @@ def products(lib, variant: int, A, B, reps: int, stream: int):
     if st != 0:
         raise RuntimeError(f"dprobe_products failed with hipError {st}")
     return C
+
+
+def factor(lib, A, X, stream: int):
+    """The engine's Cholesky factor L of A, L^-1 X, L^-T L^-1 X and the flag per
+    matrix (torch device tensors [blocks, n, n], n = 20 or 8, float64 or float32)."""
+    import torch
+    n = A.shape[1]
+    assert A.is_contiguous() and X.is_contiguous() and A.shape == X.shape and A.shape[1:] == (n, n)
+    L, Xo, Yo = torch.empty_like(A), torch.empty_like(A), torch.empty_like(A)
+    ok = torch.empty(A.shape[0], dtype=torch.int32, device="cuda")
+    st = lib.dprobe_factor(n, int(A.dtype == torch.float32), A.shape[0], A.data_ptr(), X.data_ptr(), L.data_ptr(),
+                           Xo.data_ptr(), Yo.data_ptr(), ok.data_ptr(), stream)
+    if st != 0:
+        raise RuntimeError(f"dprobe_factor failed with hipError {st}")
+    return L, Xo, Yo, ok
 
 
 def measure(blocks: int = 2048, reps: int = 64, seed: int = 0) -> dict:
