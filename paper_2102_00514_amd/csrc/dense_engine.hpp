@@ -26,7 +26,7 @@ class DenseEngine final : public EngineBase {
  public:
   static constexpr int N = Model::N, P = Model::P;
   using Lay = dn::Layout<N, P>;
-  static constexpr int kFan = 8;        // level 0: slots per wave (default)
+  static constexpr int kFan = 8;        // level 0: slots per wave where the chunks fill the chip
   static constexpr int kLevelFan = 2;   // higher levels: aggregates per wave
   static constexpr int kLevelFanS = 4;  // the same for the smoothing scan, whose combine is 4x cheaper
 
@@ -43,7 +43,7 @@ class DenseEngine final : public EngineBase {
     use_graph_ = pb.use_graph != 0;
     const int64_t nmeas = pb.offsets[ntracks];
     S = nmeas + ntracks;
-    fan0_ = pb.lane_slots >= 1 ? pb.lane_slots : kFan;
+    fan0_ = pb.lane_slots >= 1 ? pb.lane_slots : auto_fan(S, cap);
     sched_lanes = dn::kWave;
     sched_slots = fan0_;
     // scan levels
@@ -178,6 +178,21 @@ class DenseEngine final : public EngineBase {
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fail(SM_EDEVICE, hip_msg(e, "initial trajectory"));
     return SM_OK;
+  }
+
+  // Slots per wave when the caller leaves them open.  A chunk walks its slots
+  // one after the other, so while the chunks leave the 1024 SIMDs idle fewer
+  // slots each are faster, up to the scan levels they add; once they fill the
+  // chip, more slots per chunk mean fewer combines and carries above level 0.
+  // Unscented FP64, ms per iteration with 1, 2, 4, 8 slots: S = 256: 0.398 0.402
+  // 0.435 0.564; 2001: 0.626 0.574 0.620 0.734; 4001: 0.845 0.764 0.732 0.842;
+  // 8001: 1.207 1.056 1.013 1.003; 32,001: - - 2.452 2.463.  FP32 keeps eight: its
+  // results move by up to 2e-5 with the shape of the scan tree.  Smaller chunks
+  // need more aggregates; under a cap on device memory the plan stays the
+  // smaller one.
+  static int auto_fan(int64_t S, int64_t cap) {
+    if (sizeof(R) == 4 || cap > 0 || S > 12288) return kFan;
+    return S <= 3072 ? 2 : 4;
   }
 
   dn::DnArgs args() const {
