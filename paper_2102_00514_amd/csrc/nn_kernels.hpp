@@ -74,9 +74,12 @@ __device__ __forceinline__ void stage_tile(const ConvArgs& a, int t, int m0, int
   }
 }
 
-// out[m][p] = epilogue(sum_r A(m, r) B(r, p)); grid (ceil(N / 64), ceil(M / 64)).
+// out[m][p] = epilogue(sum_r A(m, r) B(r, p)), residual or backward: the layers
+// whose windows do not fill the tiles of k_conv_direct.  grid (ceil(N / 64),
+// ceil(M / 64)).
 template <int EPI>
 __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
+  static_assert(EPI == kEpiResidual || EPI == kEpiBackward, "the other layers run k_conv_direct");
   __shared__ __align__(16) float As[kTk][kTile + kPad];
   __shared__ __align__(16) float Bs[kTk][kTile];
   const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
@@ -118,18 +121,180 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
     } else {
       const float b = a.bias[m];
       v.x += b; v.y += b; v.z += b; v.w += b;
-      if (EPI == kEpiLinear) {
-        st4(a.out + o, v);
-      } else {
-        v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
-        st4(a.out + o, v);
-        if (EPI == kEpiResidual) {
-          const float4 u = ld4(a.in2 + o);
-          st4(a.out2 + o, make_float4(u.x + v.x, u.y + v.y, u.z + v.z, u.w + v.w));
+      v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
+      st4(a.out + o, v);
+      const float4 u = ld4(a.in2 + o);
+      st4(a.out2 + o, make_float4(u.x + v.x, u.y + v.y, u.z + v.z, u.w + v.w));
+    }
+  }
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
+// The same convolutions on the FP32 matrix cores, for layers whose output
+// positions are their source's (the residual layers, with KT = 3 taps, when
+// whole windows fill tiles of 64 positions; embedding and head, KT = 1).  A
+// block takes 32 PW positions and 128 output rows; up to 128 source channels
+// go through LDS as they lie in memory, so that a tap is a shifted LDS read,
+// masked at the window's edges, and no index is divided per element (the
+// gather of k_conv cost more than its multiply-adds).  The weights are packed
+// in the order in which the lanes take them (k_pack_direct) and come straight
+// from the caches: through LDS they took the registers of a second block per CU.
+// 128 x 384 x 16,384: 77 us with k_conv, 30 to 34 here; bound by the
+// products (10 us at the card's FP32 matrix rate) and 33 MB of activations.
+// 16 x 16 x 4 FP32 MFMA: lane l feeds A[l % 16][l / 16] and B[l / 16][l % 16],
+// four channels of one tap per instruction, and receives D[4 (l / 16) + q][l %
+// 16].  It adds its four products one after the other, each rounded as a
+// multiply-add, and they are taken in the order of the reduction index (channel,
+// tap), so the sums are k_conv's bit for bit, at twice the vector unit's rate.
+// Each wave owns 32 x 32 (waves without rows only stage).  grid (ceil(N / (32
+// PW)), ceil(M / 128)), 256 PW threads.
+// ---------------------------------------------------------------------------
+struct DirectArgs {
+  int M, Cin, N, Lpos;   // output rows, source channels, positions, positions per window
+  const float* W;        // packed weights (PackDirect)
+  const float* bias;     // [M] (forward epilogues)
+  const float* src;      // channel c at position p: src[(c / patch) ld + p patch + c % patch]
+  int ld, patch;
+  int dil;               // tap k reads position p + (k - 1) dil of the same window
+  float* out;            // as in ConvArgs
+  float* out2;
+  const float* in2;
+  const float* mask;
+};
+
+// A layer's weights as A fragments: word ((mt S + s) 64 + l) 4 + e, S = KT ceil(
+// Cin / 16), s = (group of 16 channels) KT + f: row 16 mt + l % 16, reduction
+// index r = 4 (4 f + e) + l / 16 of the group, channel 16 group + r / KT, tap
+// r % KT, zero past the matrix.  Row tiles are padded to pairs.
+struct PackDirect {
+  const float* W;        // [Cout][Cin][K] of the layer
+  int M, Cin, KT;        // rows and channels as the convolution sees them
+  int transposed;        // 0: A(m, c, k) = W[(m Cin + c) K + k]; 1: W[(c M + m) K + k]
+  float* out;
+};
+__host__ __device__ __forceinline__ int64_t direct_words(int M, int Cin, int KT) {
+  return int64_t((M + 31) / 32) * 2 * KT * ((Cin + 15) / 16) * 256;
+}
+constexpr int kPackMost = 32;
+struct PackDirectArgs {
+  PackDirect layer[kPackMost];
+};
+// grid (blocks, layers)
+__global__ __launch_bounds__(256) void k_pack_direct(PackDirectArgs args) {
+  const PackDirect a = args.layer[blockIdx.y];
+  const int64_t words = direct_words(a.M, a.Cin, a.KT);
+  const int S = a.KT * ((a.Cin + 15) / 16);
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < words; i += int64_t(gridDim.x) * 256) {
+    const int e = int(i & 3), l = int(i >> 2) & 63;
+    const int64_t t = i >> 8;
+    const int s = int(t % S), r = 4 * (4 * (s % a.KT) + e) + (l >> 4);
+    const int m = int(t / S) * 16 + (l & 15), c = 16 * (s / a.KT) + r / a.KT, k = r % a.KT;
+    float v = 0.f;
+    if (m < a.M && c < a.Cin)
+      v = a.W[(a.transposed ? int64_t(c) * a.M + m : int64_t(m) * a.Cin + c) * a.KT + k];
+    a.out[i] = v;
+  }
+}
+
+constexpr int kDirP = 64;    // most positions per block
+constexpr int kDirC = 128;   // source channels per stage
+
+template <int KT, int EPI, int PW>
+__global__ __launch_bounds__(256 * PW) void k_conv_direct(DirectArgs a) {
+  constexpr int T = 256 * PW, P = 32 * PW;
+  constexpr int BP = P + 16;     // row pitch: the four channel rows of a fragment on distinct banks
+  __shared__ float Bs[kDirC][BP];
+  const int t = threadIdx.x, wv = t >> 6, ln = t & 63, g = ln >> 4, lr = ln & 15;
+  const int p0 = blockIdx.x * P;
+  const int m0 = (blockIdx.y * 4 + wv / PW) * 32, pw = (wv % PW) * 32;   // this wave's part of the output
+  // Step u of a channel group takes r = 4 u + g, i.e. channel (4 u + g) / KT and
+  // tap (4 u + g) % KT: of the three cases v = u % 3 (KT = 3), this lane's LDS
+  // row past 4 u / 3, its column in each position tile, and whether that lies
+  // in the window.
+  int at[KT][2];
+  bool live[KT][2];
+#pragma unroll
+  for (int v = 0; v < KT; ++v)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = KT == 3 ? (v + g) / 3 : g, k = KT == 3 ? (v + g) % 3 : 0;
+      const int p = pw + 16 * j + lr, off = KT == 3 ? (k - 1) * a.dil : 0;
+      const int q = KT == 3 ? p % a.Lpos + off : 0;
+      live[v][j] = KT == 1 || (q >= 0 && q < a.Lpos);
+      at[v][j] = row * BP + (live[v][j] ? p + off : p);
+    }
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int S = KT * ((a.Cin + 15) / 16);
+  const bool rows = m0 < a.M;
+  const f32x4* W = reinterpret_cast<const f32x4*>(a.W) + (int64_t(rows ? m0 : 0) / 16 * S) * 64 + ln;
+  for (int c0 = 0; c0 < a.Cin; c0 += kDirC) {
+    const int cn = min(kDirC, (a.Cin - c0 + 15) & ~15);   // channels of this stage, padded to whole groups
+    if (c0 > 0) __syncthreads();
+#pragma unroll 8
+    for (int e = t; e < cn * P; e += T) {
+      const int c = c0 + e / P, p = p0 + e % P;
+      const int row = a.patch == 1 ? c : c / a.patch;
+      Bs[e / P][e % P] =
+          (c < a.Cin && p < a.N) ? a.src[size_t(row) * a.ld + size_t(p) * a.patch + (c - row * a.patch)] : 0.f;
+    }
+    __syncthreads();
+    const f32x4* w = W + int64_t(c0 / 16) * KT * 64;
+    for (int cg = 0; rows && cg < cn / 16; ++cg)
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        f32x4 x[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i] = w[(int64_t(i) * S + cg * KT + k) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int u = 4 * k + e, v = KT == 3 ? u % 3 : 0;
+          float y[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const float b = Bs[16 * cg + 4 * u / KT][at[v][j]];
+            y[j] = live[v][j] ? b : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][e], y[j], acc[i][j], 0, 0, 0);
+        }
+      }
+  }
+  if (!rows) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = m0 + 16 * i + 4 * g + q;
+      if (m >= a.M) continue;
+      const float b = EPI == kEpiBackward ? 0.f : a.bias[m];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int p = p0 + pw + 16 * j + lr;
+        if (p >= a.N) continue;
+        const size_t o = size_t(m) * a.N + p;
+        float v = acc[i][j][q];
+        if (EPI == kEpiBackward) {
+          if (a.in2) v += a.in2[o];
+          if (a.out) a.out[o] = v;
+          a.out2[o] = a.mask[o] > 0.f ? v : 0.f;
+        } else if (EPI == kEpiLinear) {
+          a.out[o] = v + b;
+        } else {
+          v = fmaxf(v + b, 0.f);
+          a.out[o] = v;
+          if (EPI == kEpiResidual) a.out2[o] = a.in2[o] + v;
         }
       }
     }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -142,7 +307,6 @@ __global__ __launch_bounds__(kThreads) void k_conv(ConvArgs a) {
 // Forward epilogues only (bias + ReLU, residual, linear).
 // ---------------------------------------------------------------------------
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ short to_bf16(float f) {
   unsigned u = __float_as_uint(f);
@@ -259,17 +423,134 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(WgradArgs a) {
   }
 }
 
-// Sums the chunk partials (in chunk order) into the flat gradient:
-// W part at w_off + m * Kr + r, bias at b_off + m.
-__global__ void k_wgrad_reduce(const float* part, int chunks, int M, int Kr, float* grad, int64_t w_off,
-                               int64_t b_off) {
-  const int R1 = Kr + 1;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= M * R1) return;
-  const int m = e / R1, r = e - m * R1;
+// Weight-gradient partials of the same layers on the FP32 matrix cores: the
+// positions are the reduction, so a lane's A is D[m][p] and its B the source
+// channel at p + (k - 1) dil, four positions per instruction; a block takes
+// 128 rows, 32 channels with all their taps, and `chunk` positions (a multiple
+// of 64), in stages of 64.  Against k_wgrad, whose gather ran once per element
+// and tile: 128 x 385 over 16,384 positions 75 us, 30 here.
+// grid (ceil(Cin / 32), ceil(M / 128), chunks).
+struct DirectWgradArgs {
+  int M, Cin, N, Lpos, chunk;
+  const float* D;        // [M][N]
+  const float* src;      // as in DirectArgs
+  int ld, patch, dil;
+  float* part;           // [chunks][M][Cin KT + 1]
+};
+
+template <int KT>
+__global__ __launch_bounds__(256) void k_wgrad_direct(DirectWgradArgs a) {
+  constexpr int T = 256, MR = 128, CR = 32;
+  constexpr int PP = kDirP + 4;     // row pitch: the 16 rows x 4 positions of a fragment on distinct banks
+  __shared__ float Ds[MR][PP];
+  __shared__ float Bs[CR][PP];
+  const int t = threadIdx.x, wv = t >> 6, ln = t & 63, g = ln >> 4, lr = ln & 15;
+  const int m0 = blockIdx.y * MR, cb = blockIdx.x * CR;
+  const int pbeg = blockIdx.z * a.chunk, pend = min(pbeg + a.chunk, a.N);
+  f32x4 acc[2][2][KT];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < KT; ++k) acc[i][j][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float bias[2] = {0.f, 0.f};
+  constexpr int DN = MR * kDirP / T, BN = CR * kDirP / T;
+  float dv[DN], bv[BN];
+  auto load = [&](int pc) {
+#pragma unroll
+    for (int i = 0; i < DN; ++i) {
+      const int e = t + T * i, m = m0 + e / kDirP, p = pc + e % kDirP;
+      dv[i] = (m < a.M && p < pend) ? a.D[size_t(m) * a.N + p] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < BN; ++i) {
+      const int e = t + T * i, c = cb + e / kDirP, p = pc + e % kDirP;
+      const int row = a.patch == 1 ? c : c / a.patch;
+      bv[i] = (c < a.Cin && p < pend) ? a.src[size_t(row) * a.ld + size_t(p) * a.patch + (c - row * a.patch)] : 0.f;
+    }
+  };
+  load(pbeg);
+  for (int pc = pbeg; pc < pend; pc += kDirP) {
+#pragma unroll
+    for (int i = 0; i < DN; ++i) Ds[(t + T * i) / kDirP][(t + T * i) % kDirP] = dv[i];
+#pragma unroll
+    for (int i = 0; i < BN; ++i) Bs[(t + T * i) / kDirP][(t + T * i) % kDirP] = bv[i];
+    __syncthreads();
+    if (pc + kDirP < pend) load(pc + kDirP);
+#pragma unroll 4
+    for (int s = 0; m0 + 32 * wv < a.M && s < kDirP / 4; ++s) {
+      const int p = 4 * s + g;
+      float x[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        x[i] = Ds[32 * wv + 16 * i + lr][p];
+        bias[i] += x[i];
+      }
+      const int w = KT == 3 ? p % a.Lpos : 0;
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        const int off = KT == 3 ? (k - 1) * a.dil : 0;
+        const bool live = KT == 1 || (w + off >= 0 && w + off < a.Lpos);
+        const int q = live ? p + off : p;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float v = Bs[16 * j + lr][q];
+          const float y = live ? v : 0.f;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) acc[i][j][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y, acc[i][j][k], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  const int Kr = a.Cin * KT;
+  float* part = a.part + size_t(blockIdx.z) * a.M * (Kr + 1);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = m0 + 32 * wv + 16 * i + 4 * g + q;
+      if (m >= a.M) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int c = cb + 16 * j + lr;
+        if (c >= a.Cin) continue;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) part[size_t(m) * (Kr + 1) + c * KT + k] = acc[i][j][k][q];
+      }
+    }
+    // bias column: the sums of D over this lane's quarter of the positions
+    float b = bias[i];
+    b += __shfl_xor(b, 16);
+    b += __shfl_xor(b, 32);
+    const int m = m0 + 32 * wv + 16 * i + lr;
+    if (blockIdx.x == 0 && g == 0 && m < a.M) part[size_t(m) * (Kr + 1) + Kr] = b;
+  }
+}
+
+// Sums the chunk partials into the flat gradient: W part at w_off + m * Kr + r,
+// bias at b_off + m.  A block takes 64 entries; its four waves sum a quarter of
+// the chunks each, in order, and the quarters are added in order.  (One thread
+// per entry over all chunks left 193 blocks waiting on 64 loads in a row: 25 us
+// for 128 x 385 over 64 chunks, 5 us now.)
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* part, int chunks, int M, int Kr, float* grad,
+                                                      int64_t w_off, int64_t b_off) {
+  __shared__ float sum[4][64];
+  const int R1 = Kr + 1, ln = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t e = int64_t(blockIdx.x) * 64 + ln, cnt = int64_t(M) * R1;
+  const int z0 = chunks * wv / 4, z1 = chunks * (wv + 1) / 4;
   float s = 0.f;
-  for (int z = 0; z < chunks; ++z) s += part[(size_t(z) * M + m) * R1 + r];
-  if (r < Kr) grad[w_off + size_t(m) * Kr + r] = s;
+  if (e < cnt) {
+#pragma unroll 8
+    for (int z = z0; z < z1; ++z) s += part[z * cnt + e];
+  }
+  sum[wv][ln] = s;
+  __syncthreads();
+  if (wv > 0 || e >= cnt) return;
+  s = ((sum[0][ln] + sum[1][ln]) + sum[2][ln]) + sum[3][ln];
+  const int64_t m = e / R1, r = e - m * R1;
+  if (r < Kr) grad[w_off + m * Kr + r] = s;
   else grad[b_off + m] = s;
 }
 

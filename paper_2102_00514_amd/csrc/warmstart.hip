@@ -57,6 +57,7 @@ int64_t total_params(const std::vector<LayerSpec>& L) { return L.back().b_off + 
 std::string hip_msg(hipError_t e, const char* what) { return std::string(what) + ": " + hipGetErrorString(e); }
 
 constexpr int kWgradTarget = 512;  // blocks aimed at per weight-gradient launch
+constexpr int kDirectTarget = 512; // the same for the matrix-core form (two blocks per CU)
 
 }  // namespace
 
@@ -79,6 +80,11 @@ struct ws_net {
   short* wt16 = nullptr;      // BF16 weights packed for k_net_mfma: embedding, residual layers, head
   bool net_fused = false;     // the inference form runs k_net_mfma (C = 128 or 256, 128 % Lpos == 0)
   bool net_packed = false;    // wt16 holds the current parameters
+  // FP32 weights packed for k_conv_direct: of each layer for the forward pass,
+  // then of each layer after the embedding for the backward one
+  float* wt32 = nullptr;
+  std::vector<float*> wt_fwd, wt_bwd;   // null: the layer does not run it
+  bool direct_packed = false;           // wt32 holds the current parameters
   int64_t part_floats = 0;
   int* win_track = nullptr;
   int* win_start = nullptr;
@@ -155,7 +161,9 @@ struct ws_net {
     }
     for (const auto& L : layers) {
       const int Kr = L.cin * L.K;
-      part_floats = std::max<int64_t>(part_floats, int64_t(wgrad_chunk_bound(L.cout, Kr, int(pos))) * L.cout * (Kr + 1));
+      int c_;
+      const int chunks = direct(L) ? direct_chunk(L, int(pos), &c_) : wgrad_chunk_bound(L.cout, Kr, int(pos));
+      part_floats = std::max<int64_t>(part_floats, int64_t(chunks) * L.cout * (Kr + 1));
     }
     A_(&part, part_floats);
     A_(&loss_part, 1024);
@@ -167,6 +175,17 @@ struct ws_net {
       for (const auto& L : layers) words += wsn::net_words(L.cout, L.cin * L.K);
       e = alloc(reinterpret_cast<void**>(&wt16), sizeof(short) * size_t(words), allocs);
     }
+    int64_t words = 0;
+    std::vector<int64_t> at;
+    for (int tr = 0; tr < 2; ++tr)
+      for (const auto& L : layers) {
+        const bool used = direct(L) && !(tr && &L == &layers.front());
+        at.push_back(used ? words : -1);
+        if (used) words += direct_words(L, tr);
+      }
+    A_(&wt32, size_t(words));
+    for (size_t i = 0; i < at.size(); ++i)
+      (i < layers.size() ? wt_fwd : wt_bwd).push_back(at[i] < 0 ? nullptr : wt32 + at[i]);
     if (e != hipSuccess)
       return fail(e == hipErrorOutOfMemory ? WS_ENOMEM : WS_EDEVICE, hip_msg(e, "device allocation"));
     std::vector<float> ones(c.nx, 1.f);
@@ -181,16 +200,16 @@ struct ws_net {
     return WS_OK;
   }
 
+  // the generic forms: FP32 (residual, backward), and BF16 products (forward)
   template <int EPI>
-  void conv(const wsn::ConvArgs& a, bool mfma = false) {
+  void conv(const wsn::ConvArgs& a) {
     const dim3 grid(unsigned((a.N + wsn::kTile - 1) / wsn::kTile), unsigned((a.M + wsn::kTile - 1) / wsn::kTile));
-    if constexpr (EPI != wsn::kEpiBackward) {
-      if (mfma) {
-        hipLaunchKernelGGL(wsn::k_conv_mfma<EPI>, grid, dim3(wsn::kThreads), 0, stream, a);
-        return;
-      }
-    }
     hipLaunchKernelGGL(wsn::k_conv<EPI>, grid, dim3(wsn::kThreads), 0, stream, a);
+  }
+  template <int EPI>
+  void conv_mfma(const wsn::ConvArgs& a) {
+    const dim3 grid(unsigned((a.N + wsn::kTile - 1) / wsn::kTile), unsigned((a.M + wsn::kTile - 1) / wsn::kTile));
+    hipLaunchKernelGGL(wsn::k_conv_mfma<EPI>, grid, dim3(wsn::kThreads), 0, stream, a);
   }
 
   wsn::Gather gather_of(const LayerSpec& L, const float* src, int n, bool transpose_taps) const {
@@ -200,28 +219,117 @@ struct ws_net {
     return {src, n * Lpos, L.K, Lpos, Lpos, 1, L.dil, L.pad};
   }
 
+  // Whether a layer runs the direct matrix-core forms: its taps stay in the
+  // window, so a tile of 64 positions has to hold whole windows; one tap needs
+  // nothing of the sort.
+  bool direct(const LayerSpec& L) const { return L.K == 1 || &L == &layers.front() || wsn::kDirP % Lpos == 0; }
+
+  // rows, channels and taps of a layer's convolution; the embedding takes each
+  // patch's steps as channels
+  wsn::PackDirect pack_of(const LayerSpec& L, bool transposed) const {
+    const bool embed = &L == &layers.front();
+    return {theta + L.w_off, transposed ? L.cin : L.cout, transposed ? L.cout : (embed ? L.cin * L.K : L.cin),
+            embed ? 1 : L.K, transposed ? 1 : 0, nullptr};
+  }
+  int64_t direct_words(const LayerSpec& L, bool transposed) const {
+    const wsn::PackDirect p = pack_of(L, transposed);
+    return wsn::direct_words(p.M, p.Cin, p.KT);
+  }
+
+  // packed copies of the weights for k_conv_direct, made again when they have changed
+  void pack_direct() {
+    if (direct_packed) return;
+    wsn::PackDirectArgs a{};
+    unsigned n = 0;
+    for (int tr = 0; tr < 2; ++tr)
+      for (size_t l = 0; l < layers.size(); ++l) {
+        float* out = (tr ? wt_bwd : wt_fwd)[l];
+        if (!out) continue;
+        a.layer[n] = pack_of(layers[l], tr != 0);
+        a.layer[n++].out = out;
+      }
+    hipLaunchKernelGGL(wsn::k_pack_direct, dim3(64, n), dim3(256), 0, stream, a);
+    direct_packed = true;
+  }
+
+  // src as the layer's channels see it
+  wsn::DirectArgs direct_args(const LayerSpec& L, const float* src, int n, bool transposed) const {
+    const bool embed = &L == &layers.front();
+    const wsn::PackDirect p = pack_of(L, transposed);
+    wsn::DirectArgs a{};
+    a.N = n * Lpos;
+    a.M = p.M;
+    a.Cin = p.Cin;
+    a.Lpos = Lpos;
+    a.W = (transposed ? wt_bwd : wt_fwd)[&L - layers.data()];
+    a.bias = theta + L.b_off;
+    a.src = src;
+    a.ld = embed ? n * cfg.window : a.N;
+    a.patch = embed ? L.K : 1;
+    a.dil = transposed ? -L.dil : L.dil;
+    return a;
+  }
+
+  template <int KT, int EPI>
+  void conv_direct_k(const wsn::DirectArgs& a) {
+    const unsigned gy = unsigned((a.M + 127) / 128);
+    if (KT == 1 || 32 % a.Lpos == 0)
+      hipLaunchKernelGGL((wsn::k_conv_direct<KT, EPI, 1>), dim3(unsigned((a.N + 31) / 32), gy), dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL((wsn::k_conv_direct<KT, EPI, 2>), dim3(unsigned((a.N + 63) / 64), gy), dim3(512), 0, stream, a);
+  }
+  template <int EPI>
+  void conv_direct(const LayerSpec& L, const wsn::DirectArgs& a) {
+    if (L.K == 3 && &L != &layers.front()) conv_direct_k<3, EPI>(a);
+    else conv_direct_k<1, EPI>(a);
+  }
+
   // xb [2 ny][n W] -> out [P nx][n L]; keeps every activation for the backward pass
-  // mfma: the inference form of the products (BF16 operands on the matrix
-  // cores, FP32 accumulation); training always runs the FP32 kernels
-  void forward(int n, bool mfma = false) {
-    const int N = n * Lpos;
+  void forward(int n) {
     const int Hn = cfg.hidden;
-    {
-      const LayerSpec& L = layers[0];
-      wsn::ConvArgs a{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, xb, n, false),
-                      H[0], nullptr, nullptr, nullptr};
-      conv<wsn::kEpiRelu>(a, mfma);
-    }
+    pack_direct();
+    wsn::DirectArgs e = direct_args(layers[0], xb, n, false);
+    e.out = H[0];
+    conv_direct<wsn::kEpiRelu>(layers[0], e);
     for (int l = 1; l <= Hn; ++l) {
       const LayerSpec& L = layers[l];
-      wsn::ConvArgs a{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, H[l - 1], n, false),
-                      A[l], H[l], H[l - 1], nullptr};
-      conv<wsn::kEpiResidual>(a, mfma);
+      if (direct(L)) {
+        wsn::DirectArgs d = direct_args(L, H[l - 1], n, false);
+        d.out = A[l];
+        d.out2 = H[l];
+        d.in2 = H[l - 1];
+        conv_direct<wsn::kEpiResidual>(L, d);
+      } else {
+        conv<wsn::kEpiResidual>({L.cout, L.cin * L.K, n * Lpos, theta + L.w_off, 0, theta + L.b_off,
+                                 gather_of(L, H[l - 1], n, false), A[l], H[l], H[l - 1], nullptr});
+      }
     }
-    const LayerSpec& L = layers[Hn + 1];
-    wsn::ConvArgs a{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, H[Hn], n, false),
-                    out, nullptr, nullptr, nullptr};
-    conv<wsn::kEpiLinear>(a, mfma);
+    wsn::DirectArgs h = direct_args(layers[Hn + 1], H[Hn], n, false);
+    h.out = out;
+    conv_direct<wsn::kEpiLinear>(layers[Hn + 1], h);
+  }
+
+  // The inference form of the products layer by layer (BF16 operands on the
+  // matrix cores, FP32 accumulation), where k_net_mfma does not apply
+  void forward_mfma(int n) {
+    const int N = n * Lpos, Hn = cfg.hidden;
+    auto args = [&](const LayerSpec& L, const float* src) {
+      return wsn::ConvArgs{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, src, n, false),
+                           nullptr, nullptr, nullptr, nullptr};
+    };
+    wsn::ConvArgs a = args(layers[0], xb);
+    a.out = H[0];
+    conv_mfma<wsn::kEpiRelu>(a);
+    for (int l = 1; l <= Hn; ++l) {
+      a = args(layers[l], H[l - 1]);
+      a.out = A[l];
+      a.out2 = H[l];
+      a.in2 = H[l - 1];
+      conv_mfma<wsn::kEpiResidual>(a);
+    }
+    a = args(layers[Hn + 1], H[Hn]);
+    a.out = out;
+    conv_mfma<wsn::kEpiLinear>(a);
   }
 
   // BF16 copies of the weights for k_net_mfma, made again when they have changed
@@ -271,16 +379,61 @@ struct ws_net {
     }
   }
 
-  void wgrad(const LayerSpec& L, const float* D, const wsn::Gather& g, int N) {
-    int chunk;
+  // Positions per block of the direct weight gradient: a multiple of the stage.
+  // The chunks of a batch never exceed those of max_batch, which size the
+  // workspace.
+  int direct_chunk(const LayerSpec& L, int N, int* chunk) const {
+    const int Kr = L.cin * L.K, KT = &L == &layers.front() ? 1 : L.K, Cin = Kr / KT;
+    const int tiles = ((Cin + 31) / 32) * ((L.cout + 127) / 128);
+    const int stages = (N + wsn::kDirP - 1) / wsn::kDirP;
+    const int most = std::min(stages, std::max(1, kDirectTarget / tiles));
+    *chunk = (stages + most - 1) / most * wsn::kDirP;
+    return (N + *chunk - 1) / *chunk;
+  }
+
+  template <int KT>
+  void wgrad_direct_k(const wsn::DirectWgradArgs& a, int chunks) {
+    hipLaunchKernelGGL(wsn::k_wgrad_direct<KT>,
+                       dim3(unsigned((a.Cin + 31) / 32), unsigned((a.M + 127) / 128), unsigned(chunks)), dim3(256), 0,
+                       stream, a);
+  }
+
+  // gradient of layer L: D [cout][N] its output's, src its input
+  void wgrad(const LayerSpec& L, const float* D, const float* src, int n) {
+    const int N = n * Lpos;
     const int Kr = L.cin * L.K;
+    if (direct(L)) {
+      const bool embed = &L == &layers.front();
+      wsn::DirectWgradArgs a{};
+      const int chunks = direct_chunk(L, N, &a.chunk);
+      a.M = L.cout;
+      a.Cin = embed ? Kr : L.cin;
+      a.N = N;
+      a.Lpos = Lpos;
+      a.D = D;
+      a.src = src;
+      a.ld = embed ? n * cfg.window : N;
+      a.patch = embed ? L.K : 1;
+      a.dil = L.dil;
+      a.part = part;
+      if (L.K == 3 && !embed) wgrad_direct_k<3>(a, chunks);
+      else wgrad_direct_k<1>(a, chunks);
+      wgrad_sum(L, chunks);
+      return;
+    }
+    const wsn::Gather g = gather_of(L, src, n, false);
+    int chunk;
     const int chunks = wgrad_chunks(L.cout, Kr, N, &chunk);
     const wsn::WgradArgs a{L.cout, Kr, N, chunk, D, g, part};
     const dim3 grid(unsigned((Kr + 1 + wsn::kTile - 1) / wsn::kTile), unsigned((L.cout + wsn::kTile - 1) / wsn::kTile),
                     unsigned(chunks));
     hipLaunchKernelGGL(wsn::k_wgrad, grid, dim3(wsn::kThreads), 0, stream, a);
-    const int cnt = L.cout * (Kr + 1);
-    hipLaunchKernelGGL(wsn::k_wgrad_reduce, dim3(unsigned((cnt + 255) / 256)), dim3(256), 0, stream,
+    wgrad_sum(L, chunks);
+  }
+
+  void wgrad_sum(const LayerSpec& L, int chunks) {
+    const int Kr = L.cin * L.K, cnt = L.cout * (Kr + 1);
+    hipLaunchKernelGGL(wsn::k_wgrad_reduce, dim3(unsigned((cnt + 63) / 64)), dim3(256), 0, stream,
                        static_cast<const float*>(part), chunks, L.cout, Kr, grad, L.w_off, L.b_off);
   }
 
@@ -295,23 +448,37 @@ struct ws_net {
     hipLaunchKernelGGL(wsn::k_sum, dim3(1), dim3(256), 0, stream, static_cast<const float*>(loss_part), blocks,
                        float(1.0 / double(count)), loss);
     const LayerSpec& LH = layers[Hn + 1];
-    wgrad(LH, dout, gather_of(LH, H[Hn], n, false), N);
+    wgrad(LH, dout, H[Hn], n);
     {
-      wsn::ConvArgs a{LH.cin, LH.cout * LH.K, N, theta + LH.w_off, 1, nullptr, gather_of(LH, dout, n, true),
-                      dh[0], dz[0], nullptr, Hn >= 1 ? A[Hn] : H[0]};
-      conv<wsn::kEpiBackward>(a);
+      wsn::DirectArgs d = direct_args(LH, dout, n, true);
+      d.out = dh[0];
+      d.out2 = dz[0];
+      d.mask = Hn >= 1 ? A[Hn] : H[0];
+      conv_direct<wsn::kEpiBackward>(LH, d);
     }
     int cur = 0;
     for (int l = Hn; l >= 1; --l) {
       const LayerSpec& L = layers[l];
-      wgrad(L, dz[cur], gather_of(L, H[l - 1], n, false), N);
+      wgrad(L, dz[cur], H[l - 1], n);
+      float* below = l > 1 ? dh[1 - cur] : nullptr;
+      const float* mask = l - 1 >= 1 ? A[l - 1] : H[0];
+      if (direct(L)) {
+        wsn::DirectArgs d = direct_args(L, dz[cur], n, true);
+        d.out = below;
+        d.out2 = dz[1 - cur];
+        d.in2 = dh[cur];
+        d.mask = mask;
+        conv_direct<wsn::kEpiBackward>(L, d);
+        cur ^= 1;
+        continue;
+      }
       wsn::ConvArgs a{L.cin, L.cout * L.K, N, theta + L.w_off, 1, nullptr, gather_of(L, dz[cur], n, true),
-                      l > 1 ? dh[1 - cur] : nullptr, dz[1 - cur], dh[cur], l - 1 >= 1 ? A[l - 1] : H[0]};
+                      below, dz[1 - cur], dh[cur], mask};
       conv<wsn::kEpiBackward>(a);
       cur ^= 1;
     }
     const LayerSpec& L0 = layers[0];
-    wgrad(L0, dz[cur], gather_of(L0, xb, n, false), N);
+    wgrad(L0, dz[cur], xb, n);
   }
 
   void gather_batch(const float* x, const float* lab, int64_t n_data, const int32_t* idx, int n) {
@@ -411,7 +578,7 @@ ws_status ws_set_params(ws_t h, const float* params, int64_t n) {
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_m, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_v, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  h->net_packed = false;
+  h->net_packed = h->direct_packed = false;
   if (e != hipSuccess) return h->fail(WS_EDEVICE, hip_msg(e, "parameter upload"));
   h->step = 0;
   return WS_OK;
@@ -520,7 +687,7 @@ ws_status ws_train_step(ws_t h, const float* d_x, const float* d_lab, int64_t n_
   hipLaunchKernelGGL(wsn::k_adam, dim3(unsigned((h->n_params + 255) / 256)), dim3(256), 0, h->stream, h->theta,
                      static_cast<const float*>(h->grad), h->adam_m, h->adam_v, h->n_params, opt->lr, opt->beta1,
                      opt->beta2, opt->eps, c1, c2);
-  h->net_packed = false;
+  h->net_packed = h->direct_packed = false;
   ws_status s = launch_status(h, "training step");
   if (s != WS_OK || !loss_out) return s;
   const hipError_t e = hipMemcpyAsync(loss_out, h->loss, sizeof(float), hipMemcpyDeviceToHost, h->stream);
@@ -580,7 +747,8 @@ static ws_status trajectory(ws_t h, const double* d_y, double* d_mean, bool mfma
     const dim3 grid(unsigned((cnt + 255) / 256));
     hipLaunchKernelGGL(wsn::k_features, grid, dim3(256), 0, h->stream, h->table(), d_y, h->cfg.ny, W, w0, nb, 1,
                        h->xb);
-    h->forward(nb, mfma);
+    if (mfma) h->forward_mfma(nb);
+    else h->forward(nb);
     hipLaunchKernelGGL(wsn::k_scatter, grid, dim3(256), 0, h->stream, h->table(), static_cast<const float*>(h->out),
                        w0, nb, W, h->cfg.patch, h->cfg.nx, static_cast<const float*>(h->mu),
                        static_cast<const float*>(h->sigma), d_mean);
