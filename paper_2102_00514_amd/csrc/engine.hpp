@@ -282,27 +282,32 @@ class Engine final : public EngineBase {
     return SM_OK;
   }
 
-  // the ladders keep one element per wavefront in LDS
-  size_t lds_filter() const { return sizeof(R) * FOp::kElemWords * (sched_.B / 64); }
-  size_t lds_smoother() const { return sizeof(R) * SOp::kElemWords * (sched_.B / 64); }
+  // LDS of a block_ladder over B lanes
+  template <class Op, int B>
+  static constexpr size_t ladder_lds() {
+    constexpr size_t bytes = sizeof(R) * Op::kElemWords * ladder_elems<Op, B>();
+    static_assert(bytes <= 160 * 1024 - 256, "LDS of a compute unit");
+    return bytes;
+  }
 
   template <int B, bool ISO, int FORM>
   hipError_t set_lds_limits_b() {
     using Fm = Form<FORM, N, R, ISO>;
+    constexpr size_t lds_f = ladder_lds<typename Fm::FOp, B>(), lds_s = ladder_lds<typename Fm::SOp, B>();
     hipError_t e = hipSuccess;
     auto set = [&](const void* f, size_t bytes) {
       if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
     };
-    set(reinterpret_cast<const void*>(&k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), lds_filter());
-    set(reinterpret_cast<const void*>(&k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), lds_filter());
+    set(reinterpret_cast<const void*>(&k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), lds_f);
+    set(reinterpret_cast<const void*>(&k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), lds_f);
     set(reinterpret_cast<const void*>(&k_forward_down_backward_up<Model, kInlineTaylor, B, R, ISO, FORM>),
-        lds_smoother());
+        lds_s);
     set(reinterpret_cast<const void*>(&k_forward_down_backward_up<Model, kStoredLin, B, R, ISO, FORM>),
-        lds_smoother());
+        lds_s);
     set(reinterpret_cast<const void*>(&k_scan_single<typename Fm::FOp, kTopB, R>),
-        sizeof(R) * FOp::kElemWords * (kTopB / 64));
+        ladder_lds<typename Fm::FOp, kTopB>());
     set(reinterpret_cast<const void*>(&k_scan_single<typename Fm::SOp, kTopB, R>),
-        sizeof(R) * SOp::kElemWords * (kTopB / 64));
+        ladder_lds<typename Fm::SOp, kTopB>());
     return e;
   }
 
@@ -410,7 +415,7 @@ class Engine final : public EngineBase {
   // Generic multi-level scan of `m` elements stored in scan order (tile aggregates).
   template <class Op>
   void run_scan(const void* elems, int64_t m, void* out, const char* const (&names)[3]) {
-    const size_t lds = sizeof(R) * Op::kElemWords * (kScanB / 64);
+    constexpr size_t lds = ladder_lds<Op, kScanB>();
     const int L = int(levels_.size());
     for (int l = 0; l + 1 < L; ++l) {
       const ScanLevel& lv = levels_[l];
@@ -477,39 +482,39 @@ class Engine final : public EngineBase {
     a.out = carry;
     a.ostride = size_t(tiles_);
     timed(names[1], tiles_ - 1, [&] {
-      hipLaunchKernelGGL((k_scan_single<Op, kTopB, R>), dim3(1), dim3(kTopB), sizeof(R) * Op::kElemWords * (kTopB / 64),
-                         stream, a);
+      constexpr size_t lds = ladder_lds<Op, kTopB>();
+      hipLaunchKernelGGL((k_scan_single<Op, kTopB, R>), dim3(1), dim3(kTopB), lds, stream, a);
     });
   }
 
   template <int B, bool ISO, int FORM>
   void launch_iteration(const FusedArgs& a) {
     using Fm = Form<FORM, N, R, ISO>;
+    constexpr size_t lds_f = ladder_lds<typename Fm::FOp, B>(), lds_s = ladder_lds<typename Fm::SOp, B>();
     static const char* const kFilterNames[3] = {"tiles_up_filter", "tiles_top_filter", "tiles_down_filter"};
     static const char* const kSmootherNames[3] = {"tiles_up_smoother", "tiles_top_smoother",
                                                   "tiles_down_smoother"};
     const dim3 grid{unsigned(tiles_)}, block{unsigned(B)};
     if (lin_ == SM_LIN_TAYLOR) {
       timed("forward_up", S, [&] {
-        hipLaunchKernelGGL((k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block, lds_filter(), stream,
-                           a);
+        hipLaunchKernelGGL((k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block, lds_f, stream, a);
       });
     } else {
       const dim3 sgrid = col_grid();
       const SlotArgs sa = slot_args(0);
       timed("linearize", S, [&] { launch_linearize(sa, sgrid); });
       timed("forward_up", S, [&] {
-        hipLaunchKernelGGL((k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), grid, block, lds_filter(), stream, a);
+        hipLaunchKernelGGL((k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), grid, block, lds_f, stream, a);
       });
     }
     scan_tiles<typename Fm::FOp>(ta_f_, tc_f_, kFilterNames);
     timed("forward_down_backward_up", S, [&] {
       if (lin_ == SM_LIN_TAYLOR)
         hipLaunchKernelGGL((k_forward_down_backward_up<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block,
-                           lds_smoother(), stream, a);
+                           lds_s, stream, a);
       else
         hipLaunchKernelGGL((k_forward_down_backward_up<Model, kStoredLin, B, R, ISO, FORM>), grid, block,
-                           lds_smoother(), stream, a);
+                           lds_s, stream, a);
     });
     scan_tiles<typename Fm::SOp>(ta_s_, tc_s_, kSmootherNames);
     timed("backward_down", S, [&] {
@@ -726,15 +731,17 @@ class Engine final : public EngineBase {
 
   template <int B, bool ISO, int FORM>
   void launch_filter_pass(const FusedArgs& a) {
+    using Fm = Form<FORM, N, R, ISO>;
+    constexpr size_t lds_f = ladder_lds<typename Fm::FOp, B>();
     static const char* const kFilterNames[3] = {"tiles_up_filter", "tiles_top_filter", "tiles_down_filter"};
     const dim3 grid{unsigned(tiles_)}, block{unsigned(B)};
     if (lin_ == SM_LIN_TAYLOR) {
-      hipLaunchKernelGGL((k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block, lds_filter(), stream, a);
+      hipLaunchKernelGGL((k_forward_up<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block, lds_f, stream, a);
     } else {
       launch_linearize(slot_args(cur_), col_grid());
-      hipLaunchKernelGGL((k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), grid, block, lds_filter(), stream, a);
+      hipLaunchKernelGGL((k_forward_up<Model, kStoredLin, B, R, ISO, FORM>), grid, block, lds_f, stream, a);
     }
-    scan_tiles<typename Form<FORM, N, R, ISO>::FOp>(ta_f_, tc_f_, kFilterNames);
+    scan_tiles<typename Fm::FOp>(ta_f_, tc_f_, kFilterNames);
     if (lin_ == SM_LIN_TAYLOR)
       hipLaunchKernelGGL((k_forward_down_filter<Model, kInlineTaylor, B, R, ISO, FORM>), grid, block, 0, stream, a);
     else

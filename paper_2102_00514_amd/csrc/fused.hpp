@@ -403,18 +403,25 @@ __global__ __launch_bounds__(B) void k_forward_up(FusedArgs a) {
     }
   }
   typename Op::Elem acc;
-  // each lane folds its K elements as they are built; the down-sweep builds
-  // them again rather than reading them back
-  build_filter_element<Model, SRC, R, FORM>(a, base, acc);
-  for (int j = 1; j < a.K; ++j) {
-    typename Op::Elem e, r;
-    build_filter_element<Model, SRC, R, FORM>(a, base + j, e);
-    Op::combine(acc, e, r);
-    acc = r;
+  // wavefronts of padding only (last tile, K = 1) hold the padding element,
+  // which is also their tile's aggregate, and stay out of the ladder
+  const int live = a.K == 1 ? wave_positions<B>(a.S, tile, lane, 1) : 64;
+  if (live == 0) {
+    prior_element<Model, R, FORM>(a, a.S, acc, true);
+  } else {
+    // each lane folds its K elements as they are built; the down-sweep builds
+    // them again rather than reading them back
+    build_filter_element<Model, SRC, R, FORM>(a, base, acc);
+    for (int j = 1; j < a.K; ++j) {
+      typename Op::Elem e, r;
+      build_filter_element<Model, SRC, R, FORM>(a, base + j, e);
+      Op::combine(acc, e, r);
+      acc = r;
+    }
   }
   typename Op::Elem ex;
   bool has_ex;
-  block_ladder<Op, B, true, R>(lds, acc, ex, has_ex, true, a.K > 1);
+  block_ladder<Op, B, true, R>(lds, acc, ex, has_ex, live > 0, a.K > 1, 0, live);
   // K = 1: the lane's inclusive prefix goes to the down-sweep, which then
   // needs neither the element nor a second carry application; K > 1: the
   // exclusive prefix, continued there over the rebuilt elements
@@ -481,49 +488,58 @@ __global__ __launch_bounds__(B) void k_forward_down_backward_up(FusedArgs a) {
       return;
     }
   }
-  typename FOp::Carry c;
-  bool have;
-  lane_filter_carry<N, B, R, ISO, FORM>(a, tile, lane, c, have);
   typename SOp::Elem sacc;
-  const int64_t cbase = tile * B * a.K + lane;
-  walk_lane<Model, SRC, R, ISO, FORM>(
-      a, base, cbase, B, c, have,
-      [&](int j, int64_t s, int64_t cs, const typename FOp::Carry& cj, unsigned fl, R(&F)[N][N], R(&cc)[N],
-          R(&Qp)[N][N]) {
-        if (a.filt && !(fl & kSlotFrozen)) Fm::store_moments(static_cast<R*>(a.filt), st, cs, cj);
-        typename SOp::Elem se;
-        bool loaded = false;
-        if (fl & kSlotFrozen) {
-          // padding end element (0, 0, I) in place of the frozen slot's
-          typename FOp::Elem pe;
-          typename FOp::Carry pc;
-          prior_element<Model, R, FORM>(a, a.S, pe, true);
-          FOp::to_carry(pe, pc);
-          Fm::last(pc, se);
-        } else if (fl & kSlotLast) {
-          Fm::last(cj, se);
-        } else {
-          transition_of<Model, SRC, R>(a, cs, F, cc, Qp);
-          loaded = true;
-          const bool ok = Fm::smoother(cj, F, cc, Qp, se);
-          if (!ok) se.g[0] = quiet_nan<R>();
-        }
-        if (a.K > 1) SOp::store(static_cast<R*>(a.selem), st, cs, se);
-        // paper order: sacc covers earlier slots, so sacc <- sacc (x) se, i.e.
-        // the scan-order combine with se first
-        if (j == 0) {
-          sacc = se;
-        } else {
-          typename SOp::Elem r;
-          SOp::combine(se, sacc, r);
-          sacc = r;
-        }
-        (void)s;
-        return loaded;
-      });
+  // wavefronts of padding only (last tile, K = 1) come first in the reverse
+  // order; every prefix over real slots restarts at the end element of its
+  // track, so they stay out of the ladder and write nothing
+  const bool live = a.K > 1 || tile * B + (lane & ~63) < a.S;
+  const int64_t real = a.S - tile * B;   // real slots of the tile (K = 1)
+  const int pad_waves = a.K > 1 || real >= B ? 0 : B / 64 - int((real + 63) / 64);
+  if (live) {
+    typename FOp::Carry c;
+    bool have;
+    lane_filter_carry<N, B, R, ISO, FORM>(a, tile, lane, c, have);
+    const int64_t cbase = tile * B * a.K + lane;
+    walk_lane<Model, SRC, R, ISO, FORM>(
+        a, base, cbase, B, c, have,
+        [&](int j, int64_t s, int64_t cs, const typename FOp::Carry& cj, unsigned fl, R(&F)[N][N], R(&cc)[N],
+            R(&Qp)[N][N]) {
+          if (a.filt && !(fl & kSlotFrozen)) Fm::store_moments(static_cast<R*>(a.filt), st, cs, cj);
+          typename SOp::Elem se;
+          bool loaded = false;
+          if (fl & kSlotFrozen) {
+            // padding end element (0, 0, I) in place of the frozen slot's
+            typename FOp::Elem pe;
+            typename FOp::Carry pc;
+            prior_element<Model, R, FORM>(a, a.S, pe, true);
+            FOp::to_carry(pe, pc);
+            Fm::last(pc, se);
+          } else if (fl & kSlotLast) {
+            Fm::last(cj, se);
+          } else {
+            transition_of<Model, SRC, R>(a, cs, F, cc, Qp);
+            loaded = true;
+            const bool ok = Fm::smoother(cj, F, cc, Qp, se);
+            if (!ok) se.g[0] = quiet_nan<R>();
+          }
+          if (a.K > 1) SOp::store(static_cast<R*>(a.selem), st, cs, se);
+          // paper order: sacc covers earlier slots, so sacc <- sacc (x) se, i.e.
+          // the scan-order combine with se first
+          if (j == 0) {
+            sacc = se;
+          } else {
+            typename SOp::Elem r;
+            SOp::combine(se, sacc, r);
+            sacc = r;
+          }
+          (void)s;
+          return loaded;
+        });
+  }
   typename SOp::Elem ex;
   bool has_ex;
-  block_ladder<SOp, B, false, R>(lds, sacc, ex, has_ex, true, a.K > 1);
+  block_ladder<SOp, B, false, R>(lds, sacc, ex, has_ex, live, a.K > 1, pad_waves);
+  if (!live) return;
   // as in the forward direction: inclusive prefix for K = 1, exclusive otherwise
   if (a.K == 1) SOp::store(static_cast<R*>(a.lx_s), size_t(a.tiles) * B, rt * B + rl, sacc);
   else if (has_ex) SOp::store(static_cast<R*>(a.lx_s), size_t(a.tiles) * B, rt * B + rl, ex);
@@ -597,7 +613,7 @@ __global__ __launch_bounds__(B) void k_backward_down(FusedArgs a) {
     SOp::load(static_cast<const R*>(a.tc_s), size_t(a.tiles), rt - 1, c);
     have = true;
   }
-  if (a.K == 1 || rl > 0) {
+  if (a.K == 1 ? base < a.S : rl > 0) {
     typename SOp::Elem ex;
     SOp::load(static_cast<const R*>(a.lx_s), size_t(a.tiles) * B, rt * B + rl, ex);
     if (have) {

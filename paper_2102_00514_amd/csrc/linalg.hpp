@@ -246,4 +246,11 @@ PKS_DEV void st_sym(R* __restrict__ base, size_t stride, size_t s, const R (&A)[
     PKS_UNROLL for (int j = i; j < N; ++j) base[sym_index<N>(i, j) * stride + s] = A[i][j];
 }
 
+// LDS accesses on the two sides of this point stay in their order (no
+// instruction: a wavefront's LDS accesses are executed in program order).
+PKS_DEV void order_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace pks

@@ -58,6 +58,8 @@ struct FilterCarry {
 // per cent).
 template <int N, typename R, bool kIsolate = true>
 struct FilterOp {
+  // FP64: the wavefront ladder keeps the elements in LDS (combine_at)
+  static constexpr bool kInLds = sizeof(R) == 8;
   // the scan ladders keep one copy of the operator instead of unrolling it
   static constexpr bool kCompact = false;
   using Elem = FilterElem<N, R>;
@@ -155,6 +157,27 @@ struct FilterOp {
     return ok;
   }
 
+  // With D = A_i - Z (left in Z):  eta_ij = D^T v + eta_i,  J_ij = Y^T D + J_i,
+  // the same as A_i^T v - Y^T u + eta_i and A_i^T Y - Y^T Z + J_i (Z = M Y,
+  // u = M v, M and A_i^T Y symmetric) in 100 products less of 1285 (n = 5).
+  // FP32 keeps the longer forms: its results stay what they were bit for bit.
+  static PKS_DEV void join_info(const R (&A)[N][N], const R (&Y)[N][N], const R (&v)[N], const R (&eta)[N],
+                                const R (&J)[N][N], R (&Z)[N][N], R (&oe)[N], R (&oJ)[N][N]) {
+    PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) Z[i][j] = A[i][j] - Z[i][j];
+    PKS_UNROLL for (int i = 0; i < N; ++i) {
+      R s = eta[i];
+      PKS_UNROLL for (int t = 0; t < N; ++t) s += Z[t][i] * v[t];
+      oe[i] = s;
+    }
+    PKS_UNROLL for (int a = 0; a < N; ++a)
+      PKS_UNROLL for (int b = a; b < N; ++b) {
+        R s = J[a][b];
+        PKS_UNROLL for (int t = 0; t < N; ++t) s += Y[t][a] * Z[t][b];
+        oJ[a][b] = s;
+        oJ[b][a] = s;
+      }
+  }
+
   // out = l (x) r
   static PKS_DEV void combine(const Elem& l, const Elem& r, Elem& o) {
     if (restarts(r.A)) {
@@ -173,20 +196,25 @@ struct FilterOp {
       v[i] = s;
     }
     mat_vec<N, N>(M, v, u);
-    // eta_ij = A_i^T v - Y^T u + eta_i
-    PKS_UNROLL for (int i = 0; i < N; ++i) {
-      R s = l.eta[i];
-      PKS_UNROLL for (int t = 0; t < N; ++t) s += l.A[t][i] * v[t] - Y[t][i] * u[t];
-      o.eta[i] = s;
-    }
-    // J_ij = A_i^T Y - Y^T Z + J_i
-    PKS_UNROLL for (int a = 0; a < N; ++a)
-      PKS_UNROLL for (int b = a; b < N; ++b) {
-        R s = l.J[a][b];
-        PKS_UNROLL for (int t = 0; t < N; ++t) s += l.A[t][a] * Y[t][b] - Y[t][a] * Z[t][b];
-        o.J[a][b] = s;
-        o.J[b][a] = s;
+    if constexpr (kInLds) {
+      join_info(l.A, Y, v, l.eta, l.J, Z, o.eta, o.J);
+    } else {
+      // eta_ij = A_i^T v - Y^T u + eta_i
+      PKS_UNROLL for (int i = 0; i < N; ++i) {
+        R s = l.eta[i];
+        PKS_UNROLL for (int t = 0; t < N; ++t) s += l.A[t][i] * v[t] - Y[t][i] * u[t];
+        o.eta[i] = s;
       }
+      // J_ij = A_i^T Y - Y^T Z + J_i
+      PKS_UNROLL for (int a = 0; a < N; ++a)
+        PKS_UNROLL for (int b = a; b < N; ++b) {
+          R s = l.J[a][b];
+          PKS_UNROLL for (int t = 0; t < N; ++t) s += l.A[t][a] * Y[t][b] - Y[t][a] * Z[t][b];
+          o.J[a][b] = s;
+          o.J[b][a] = s;
+        }
+      PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) Z[i][j] = l.A[i][j] - Z[i][j];
+    }
     // b_ij = A_j (b_i + u) + b_j
     PKS_UNROLL for (int i = 0; i < N; ++i) u[i] += l.b[i];
     PKS_UNROLL for (int i = 0; i < N; ++i) {
@@ -195,11 +223,61 @@ struct FilterOp {
       o.b[i] = s;
     }
     // A_ij = A_j (A_i - Z)
-    PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) Z[i][j] = l.A[i][j] - Z[i][j];
     mat_mul<N, N, N>(r.A, Z, o.A);
     // C_ij = A_j M A_j^T + C_j
     sandwich_add<N, N>(r.A, M, r.C, o.C);
     if (!ok) o.b[0] = quiet_nan<R>();
+  }
+
+  // combine on elements kept in LDS (64 to an entry): element i of p becomes
+  // (element li of lp) (x) (element i of p).  Lanes run in step, and every lane
+  // reads a word of its left element before any lane writes that word.  Both
+  // operands are read where they are used and each block is written as soon as
+  // it is there: with both in registers next to the lane moves of the ladder
+  // step the combine needed more than the 256 vector registers.
+  static PKS_DEV void combine_at(R* p, size_t i, const R* lp, size_t li) {
+    constexpr size_t st = 64;
+    R *pA = p, *pb = p + N * N * st, *pC = pb + N * st, *pe = pC + kS * st, *pJ = pe + N * st;
+    const R *lA = lp, *lb = lp + N * N * st, *lC = lb + N * st, *le = lC + kS * st, *lJ = le + N * st;
+    R A[N][N];
+    if constexpr (kIsolate) {
+      ld_mat<N, N>(pA, st, i, A);
+      if (restarts(A)) return;
+      order_lds();
+    }
+    R C[N][N], J[N][N], M[N][N], b[N], e[N], v[N], u[N];
+    ld_sym<N>(lC, st, li, C);
+    ld_sym<N>(pJ, st, i, J);
+    ld_vec<N>(lb, st, li, b);
+    ld_vec<N>(pe, st, i, e);
+    const bool ok = core(C, J, M);
+    // v = eta_j - J_j b_i, u = b_i + M v
+    PKS_UNROLL for (int a = 0; a < N; ++a) {
+      R s = e[a];
+      PKS_UNROLL for (int t = 0; t < N; ++t) s -= J[a][t] * b[t];
+      v[a] = s;
+    }
+    mat_vec<N, N>(M, v, u);
+    PKS_UNROLL for (int a = 0; a < N; ++a) u[a] += b[a];
+    R Y[N][N], Z[N][N];
+    ld_mat<N, N>(lA, st, li, A);
+    mat_mul<N, N, N>(J, A, Y);
+    mat_mul<N, N, N>(M, Y, Z);
+    ld_vec<N>(le, st, li, e);
+    ld_sym<N>(lJ, st, li, C);
+    join_info(A, Y, v, e, C, Z, e, J);
+    st_vec<N>(pe, st, i, e);
+    st_sym<N>(pJ, st, i, J);
+    ld_mat<N, N>(pA, st, i, A);
+    ld_vec<N>(pb, st, i, b);
+    PKS_UNROLL for (int a = 0; a < N; ++a) PKS_UNROLL for (int t = 0; t < N; ++t) b[a] += A[a][t] * u[t];
+    if (!ok) b[0] = quiet_nan<R>();
+    st_vec<N>(pb, st, i, b);
+    mat_mul<N, N, N>(A, Z, Y);
+    st_mat<N, N>(pA, st, i, Y);
+    ld_sym<N>(pC, st, i, C);
+    sandwich_add<N, N>(A, M, C, J);
+    st_sym<N>(pC, st, i, J);
   }
 
   // out = c (x) r for a carry c
@@ -242,6 +320,7 @@ struct SmootherCarry {
 
 template <int N, typename R, bool kIsolate = true>
 struct SmootherOp {
+  static constexpr bool kInLds = false;
   // the scan ladders keep one copy of the operator instead of unrolling it
   static constexpr bool kCompact = false;
   using Elem = SmootherElem<N, R>;

@@ -111,50 +111,127 @@ PKS_DEV bool ladder_step(int s, int wl, const typename Op::Elem& v, typename Op:
   return s == 4 ? (qrow & 1) != 0 : qrow >= 2;
 }
 
+// The same step for elements in LDS: the lane whose element is the left
+// operand of lane wl (where it combines at the step).  Same association as
+// ladder_step.
+template <bool FWD>
+PKS_DEV bool ladder_source(int s, int wl, int& src) {
+  const int in_row = FWD ? (wl & 15) : 15 - (wl & 15);
+  const int row = wl >> 4, qrow = FWD ? row : 3 - row;
+  if (s < 4) {
+    src = FWD ? wl - (1 << s) : wl + (1 << s);
+    return in_row >= (1 << s);
+  }
+  if (s == 4) {
+    src = FWD ? (row << 4) - 1 : (row + 1) << 4;
+    return (qrow & 1) != 0;
+  }
+  src = FWD ? 31 : 32;
+  return qrow >= 2;
+}
+
+// Elements a block of B lanes keeps in LDS for block_ladder: every lane's and
+// one total per wavefront (kInLds), or the totals only.
+template <class Op, int B>
+constexpr int ladder_elems() {
+  return Op::kInLds ? B + (B > 64 ? B / 64 : 0) : B / 64;
+}
+
 // Inclusive scan of the B lane values of a block.  Scan position q = lane
 // (FWD) or B-1-lane (reverse).  Inside a wavefront the six Kogge-Stone steps
-// of ladder_step move elements between lanes without LDS or barriers; across
-// wavefronts (B > 64) only each wavefront's total goes through LDS: lds holds
-// B/64 elements, entry-major with row stride B/64.  On exit v is the inclusive
-// prefix at q and, when want_ex and has_ex (q > 0), ex the exclusive one.
+// need no barrier; across wavefronts (B > 64) each wavefront's total goes
+// through LDS.  lds holds ladder_elems() elements, entry-major: first the
+// lanes' (kInLds, 64 per wavefront and entry), then the totals (row stride
+// B/64).  On exit v is the inclusive prefix at q and, when want_ex and has_ex
+// (q > 0), ex the exclusive one.
 // Invalid lanes must form a suffix of the scan order: no valid lane reads
 // their values.  A wavefront whose lanes are all invalid passes active =
 // false (wavefront-uniform): it skips its combines and only takes part in the
-// barrier.
+// barriers.  Wavefronts before first_wave in scan order may be inactive too:
+// the scan then starts at that wavefront.  nvalid (wavefront-uniform, forward
+// only) bounds the valid positions of this wavefront: steps whose distance
+// reaches it change no valid lane and are left out.
+//
+// A block of one wavefront per SIMD is bound by its longest chain of combines
+// (n = 5, FP64: 3.1 us a filtering combine, of which 2.1 us are its 1190
+// multiply-adds; 3.7 us with the operands in registers and lane moves between
+// them).  Four wavefronts without exclusive prefixes therefore join their
+// totals in two rounds, pairs first, instead of the last wavefront folding
+// three totals in turn: eight combines instead of nine.  One track, FP64:
+// forward_up 43.6 us before, 39.5 us now at T = 32768; 37.5 and 31.1 us at
+// T = 100, where two of the four wavefronts hold padding only.  FP32 keeps
+// lane moves and the order of the fold, so that its results stay what they
+// were bit for bit.
 template <class Op, int B, bool FWD, typename R>
 PKS_DEV void block_ladder(R* lds, typename Op::Elem& v, typename Op::Elem& ex, bool& has_ex, bool active = true,
-                          bool want_ex = true) {
+                          bool want_ex = true, int first_wave = 0, int nvalid = 64) {
   constexpr int NW = B / 64;
   static_assert(B % 64 == 0, "whole wavefronts");
   const int pl = int(threadIdx.x), wl = pl & 63, w = pl >> 6;
   const int qw = FWD ? wl : 63 - wl;        // scan position inside the wavefront
   const int qwave = FWD ? w : NW - 1 - w;   // scan position of the wavefront
+  constexpr size_t kRegion = size_t(Op::kElemWords) * 64;
+  R* const mine = lds + (Op::kInLds ? w * kRegion : 0);
+  R* const totals = lds + (Op::kInLds ? NW * kRegion : 0);
+  has_ex = false;
   if (active) {
-    auto step = [&](int s) {
-      typename Op::Elem left;
-      if (ladder_step<Op, FWD>(s, wl, v, left)) {
-        typename Op::Elem r;
-        Op::combine(left, v, r);
-        v = r;
-      }
-    };
-    if constexpr (Op::kCompact) {
-      // one copy of a long operator instead of six
+    if constexpr (Op::kInLds) {
+      Op::store(mine, 64, wl, v);
 #pragma unroll 1
-      for (int s = 0; s < 6; ++s) step(s);
+      for (int s = 0; s < 6; ++s) {
+        if ((1 << s) >= nvalid) break;
+        int src;
+        order_lds();
+        if (ladder_source<FWD>(s, wl, src)) Op::combine_at(mine, wl, mine, src);
+      }
+      order_lds();
     } else {
-      PKS_UNROLL for (int s = 0; s < 6; ++s) step(s);
+      auto step = [&](int s) {
+        typename Op::Elem left;
+        if (ladder_step<Op, FWD>(s, wl, v, left)) {
+          typename Op::Elem r;
+          Op::combine(left, v, r);
+          v = r;
+        }
+      };
+      if constexpr (Op::kCompact) {
+        // one copy of a long operator instead of six
+#pragma unroll 1
+        for (int s = 0; s < 6; ++s) {
+          if ((1 << s) >= nvalid) break;
+          step(s);
+        }
+      } else {
+        PKS_UNROLL for (int s = 0; s < 6; ++s)
+          if ((1 << s) < nvalid) step(s);
+      }
     }
   }
-  typename Op::Elem wp;   // total of the wavefronts before this one (qwave > 0)
+  if constexpr (Op::kInLds && NW == 4) {
+    if (!want_ex) {
+      constexpr int kLast = FWD ? 63 : 0;   // lane of a wavefront's last position
+      auto region = [&](int q) { return lds + (FWD ? q : NW - 1 - q) * kRegion; };
+      __syncthreads();
+      if (active && (qwave & 1) && qwave > first_wave) Op::combine_at(mine, wl, region(qwave - 1), kLast);
+      __syncthreads();
+      if (active && qwave >= 2 && first_wave < 2) Op::combine_at(mine, wl, region(1), kLast);
+      order_lds();
+      if (active) Op::load(mine, 64, wl, v);
+      return;
+    }
+  }
+  if constexpr (Op::kInLds) {
+    if (active) Op::load(mine, 64, wl, v);
+  }
+  typename Op::Elem wp;   // total of the wavefronts before this one (qwave > first_wave)
   if constexpr (NW > 1) {
-    if (active && qw == 63) Op::store(lds, NW, qwave, v);
+    if (active && qw == 63) Op::store(totals, NW, qwave, v);
     __syncthreads();
-    if (active && qwave > 0) {
-      Op::load(lds, NW, 0, wp);
-      for (int k = 1; k < qwave; ++k) {
+    if (active && qwave > first_wave) {
+      Op::load(totals, NW, first_wave, wp);
+      for (int k = first_wave + 1; k < qwave; ++k) {
         typename Op::Elem t, r;
-        Op::load(lds, NW, k, t);
+        Op::load(totals, NW, k, t);
         Op::combine(wp, t, r);
         wp = r;
       }
@@ -163,18 +240,34 @@ PKS_DEV void block_ladder(R* lds, typename Op::Elem& v, typename Op::Elem& ex, b
       v = r;
     }
   }
-  has_ex = false;
   if (!active || !want_ex) return;
-  // the previous lane's inclusive prefix: wave_shr:1 / wave_shl:1
-  if constexpr (FWD) Op::move(v, DppMove<0x138, 0xf>{}, ex);
-  else Op::move(v, DppMove<0x130, 0xf>{}, ex);
+  // the previous lane's inclusive prefix
   has_ex = qw > 0;
+  if constexpr (Op::kInLds) {
+    if constexpr (NW > 1) {
+      Op::store(mine, 64, wl, v);
+      order_lds();
+    }
+    if (has_ex) Op::load(mine, 64, FWD ? wl - 1 : wl + 1, ex);
+  } else {
+    // wave_shr:1 / wave_shl:1
+    if constexpr (FWD) Op::move(v, DppMove<0x138, 0xf>{}, ex);
+    else Op::move(v, DppMove<0x130, 0xf>{}, ex);
+  }
   if constexpr (NW > 1) {
-    if (qw == 0 && qwave > 0) {
+    if (qw == 0 && qwave > first_wave) {
       ex = wp;
       has_ex = true;
     }
   }
+}
+
+// Lanes of this lane's wavefront that hold positions when m positions are cut
+// into tiles of B lanes x K positions (64 or more: all of them).
+template <int B>
+PKS_DEV int wave_positions(int64_t m, int64_t tile, int lane, int K) {
+  const int64_t left = m - (tile * B + (lane & ~63)) * K;
+  return left >= int64_t(64) * K ? 64 : left > 0 ? int((left + K - 1) / K) : 0;
 }
 
 template <class Op, int B, typename R>
@@ -201,8 +294,8 @@ __global__ __launch_bounds__(B) void k_scan_up(ScanArgs a) {
   }
   typename Op::Elem ex;
   bool has_ex;
-  const bool wave_active = (tile * B + (lane & ~63)) * a.K < a.m;
-  block_ladder<Op, B, true, R>(lds, v, ex, has_ex, wave_active);
+  const int live = wave_positions<B>(a.m, tile, lane, a.K);
+  block_ladder<Op, B, true, R>(lds, v, ex, has_ex, live > 0, true, 0, live);
   R* LX = static_cast<R*>(a.lane_excl);
   if (valid && has_ex) Op::store(LX, a.lstride, tile * B + lane, ex);
   // last valid lane of the tile publishes the tile aggregate
@@ -283,7 +376,8 @@ PKS_DEV void block_scan(R* lds, int lane, const R* E, size_t estride, int64_t m,
   }
   typename Op::Elem ex;
   bool has_ex;
-  block_ladder<Op, B, true, R>(lds, v, ex, has_ex, int64_t(lane & ~63) * K < m, K > 1);
+  const int live = wave_positions<B>(m, 0, lane, K);
+  block_ladder<Op, B, true, R>(lds, v, ex, has_ex, live > 0, K > 1, 0, live);
   if (!valid) return;
   if (K == 1) {
     // v is the inclusive prefix of this lane's position, and it starts at a

@@ -196,6 +196,7 @@ struct SqrtFilterCarry {
 
 template <int N, typename R, bool kIsolate = true>
 struct SqrtFilterOp {
+  static constexpr bool kInLds = false;
   // the scan ladders keep one copy of the operator instead of unrolling it
   static constexpr bool kCompact = true;
   using Elem = SqrtFilterElem<N, R>;
@@ -400,6 +401,7 @@ struct SqrtSmootherCarry {
 
 template <int N, typename R, bool kIsolate = true>
 struct SqrtSmootherOp {
+  static constexpr bool kInLds = false;
   // the scan ladders keep one copy of the operator instead of unrolling it
   static constexpr bool kCompact = true;
   using Elem = SqrtSmootherElem<N, R>;

@@ -1,0 +1,52 @@
+"""The scan ladders at the edges of their wavefronts: tiles whose last wavefronts
+hold few real slots or none, two and four wavefronts joined, one to three tiles,
+and tile aggregates that fill the single-block scan's first wavefront exactly or
+by one more.  The parallel scans are compared with the sequential ones.
+
+Both evaluate the same smoother in FP64 from the same starting trajectory; a
+scan of S slots accumulates at most S roundings, amplified by the ratio of the
+largest to the smallest covariance entry (1e4 here): 513 * 2.2e-16 * 1e4 = 1.1e-9
+relative to the largest value of a component.  Past a few hundred slots the
+smoother has forgotten a rounding, so the bound holds for the long tracks too."""
+import numpy as np
+import pytest
+
+from paper_2102_00514_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TOL = 513 * 2.0 ** -52 * 1e4
+LENGTHS = (1, 15, 16, 31, 32, 62, 63, 64, 127, 128, 191, 192, 255, 256, 300, 512, 64 * 256, 65 * 256)
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    from paper_2102_00514_amd import binding
+    return binding
+
+
+def _run(B, pb, **kw):
+    with B.Smoother(pb, n_iter=2, **kw) as sm:
+        sm.iterate(2, want_delta=False)
+        return sm.result()
+
+
+def _compare(B, pb, **kw):
+    m, c = _run(B, pb, **kw)
+    ms, cs = _run(B, pb, scan="sequential", **kw)
+    for got, want in ((m, ms), (c.reshape(len(m), -1), cs.reshape(len(m), -1))):
+        scale = np.abs(want).max(axis=0)
+        assert np.all(np.abs(got - want) <= TOL * scale)
+
+
+@pytest.mark.parametrize("T", LENGTHS)
+def test_one_track(B, T):
+    _compare(B, wl.ct_bearings(T, seed=300 + T), lin="taylor")
+
+
+@pytest.mark.parametrize("last", (1, 63, 64, 130))
+def test_batch(B, last):
+    tracks = [wl.ct_bearings(T, seed=400 + T) for T in (250, 3, 70, last)]
+    _compare(B, wl.concat_tracks(tracks, "ladder"), lin="cubature")
