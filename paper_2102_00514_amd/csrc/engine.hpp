@@ -91,8 +91,7 @@ class Engine final : public EngineBase {
   static constexpr int kTrajW = N + kSN;
   using FOp = FilterOp<N, R>;
   using SOp = SmootherOp<N, R>;
-  using LL = LinLayout<N, P>;
-  using TL = TransLayout<N>;
+  using Rows = LinRows<Model, R>;
 
   sm_status setup(const sm_problem& pb, hipStream_t st) override {
     stream = st;
@@ -190,7 +189,7 @@ class Engine final : public EngineBase {
     A(reinterpret_cast<void**>(&delta_bits), sizeof(unsigned long long) * (ntracks + 1));
     if (seq_) {
       A(&d_traj_[1], sizeof(R) * kTrajW * stride);
-      A(&d_lin_, sizeof(R) * LL::kWords * stride);
+      A(&d_lin_, sizeof(R) * Rows::kWords * stride);
       A(&d_filt_, sizeof(R) * kTrajW * stride);
     } else {
       const size_t lanes = size_t(tiles_) * sched_.B;
@@ -198,7 +197,7 @@ class Engine final : public EngineBase {
       // sigma-point linearisation runs as its own pass, whose arrays start with
       // the transition rows
       if (lin_ != SM_LIN_TAYLOR) {
-        A(&d_lin_, sizeof(R) * LL::kWords * stride);
+        A(&d_lin_, sizeof(R) * Rows::kWords * stride);
         d_trans_ = d_lin_;
       }
       // filtering elements are built again by the down-sweeps, never stored;
@@ -547,7 +546,7 @@ class Engine final : public EngineBase {
         });
         timed("linearize", S, [&] { launch_linearize(a, grid); });
         timed("sequential", S, [&] {
-          hipLaunchKernelGGL((k_sequential<N, P, R>), dim3((ntracks + 63) / 64), dim3(64), 0, stream, a,
+          hipLaunchKernelGGL((k_sequential<Model, R>), dim3((ntracks + 63) / 64), dim3(64), 0, stream, a,
                              d_slot_off_, ntracks);
         });
         timed("delta", S, [&] { hipLaunchKernelGGL((k_delta<N, R>), grid, dim3(kSlotBlock), 0, stream, a); });
@@ -687,7 +686,7 @@ class Engine final : public EngineBase {
       a.lm = 0.0;
       a.lm_track = nullptr;
       launch_linearize(a, grid);
-      hipLaunchKernelGGL((k_sequential<N, P, R>), dim3((ntracks + 63) / 64), dim3(64), 0, stream, a, d_slot_off_,
+      hipLaunchKernelGGL((k_sequential<Model, R>), dim3((ntracks + 63) / 64), dim3(64), 0, stream, a, d_slot_off_,
                          ntracks);
       la.trans = d_lin_;
       la.lin = d_lin_;

@@ -77,7 +77,7 @@ struct FusedArgs {
   const void* P0;       // [s(N)][ntracks]
   const void* yslot;    // [P][stride]
   void* traj;           // [N + s(N)][stride]  xbar, Pbar (read by the forward kernel, updated in place at the end)
-  const void* trans;    // sigma points: the linearisation pass's rows (LinLayout); Taylor: null
+  const void* trans;    // sigma points: the linearisation pass's rows (LinRows); Taylor: null
   void* selem;          // [SmootherOp words][stride] (K > 1)
   void* filt;           // optional [N + s(N)][stride]  x*, P*
   void *lx_f, *ta_f, *tc_f;  // forward lane exclusives [words][tiles*B], tile aggregates, tile carries
@@ -114,24 +114,63 @@ PKS_DEV int tile_freeze_state(const FusedArgs& a, int64_t lo, int64_t n) {
   return any_active ? (any_frozen ? kTileMixed : kTileActive) : kTileFrozen;
 }
 
-// Linearisation arrays written by the separate linearisation pass: transition
-// out of the slot F (N*N), c (N), Q' (s(N)); measurement at the slot H (P*N),
-// d (P), R' (s(P)), ytil (P).
-template <int N, int P>
-struct LinLayout {
-  static constexpr int kF = 0;
-  static constexpr int kc = kF + N * N;
-  static constexpr int kQ = kc + N;
-  static constexpr int kH = kQ + sym_size<N>();
-  static constexpr int kd = kH + P * N;
+// Rows written by the separate linearisation pass: the transition out of the
+// slot F, c, Q' and the measurement at the slot H, d, R', ytil.
+//
+// One coordinated-turn target leaves its turn rate as it is and its bearings
+// depend on the position only, and any regression reproduces a linear
+// component: row 4 of F is e_4, c_4 is 0, row 4 of Q' is that of Q, and
+// columns 2-4 of H are zero (the points of the columns 2-4 of a lower factor
+// do not move the position).  Those 17 of the 62 words are not stored (FP64;
+// FP32 keeps all rows, so that its results stay what they were bit for bit).
+// The pass is bound by its bytes (20 words read, 62 written before, 45 now):
+// 512 ragged tracks, 2.09 M slots, cubature: 391 us before, 267 us now; the
+// kernels that read the rows are bound by their arithmetic and stay.
+template <class Model, typename R>
+struct LinRows {
+  static constexpr int N = Model::N, P = Model::P;
+  static constexpr bool kShort = Model::kFixedRate && sizeof(R) == 8;
+  static constexpr int NF = kShort ? N - 1 : N;   // stored rows of F, c, Q'
+  static constexpr int NH = kShort ? 2 : N;       // stored columns of H
+  static constexpr int kc = NF * N;
+  static constexpr int kQ = kc + NF;
+  static constexpr int kH = kQ + sym_size<NF>();
+  static constexpr int kd = kH + P * NH;
   static constexpr int kR = kd + P;
   static constexpr int ky = kR + sym_size<P>();
   static constexpr int kWords = ky + P;
-};
 
-template <int N>
-struct TransLayout {
-  static constexpr int kF = 0, kc = N * N, kQ = N * N + N, kWords = N * N + N + sym_size<N>();
+  static PKS_DEV void store_f(R* p, size_t st, size_t i, const R (&F)[N][N], const R (&c)[N], const R (&Qp)[N][N]) {
+    PKS_UNROLL for (int a = 0; a < NF; ++a) {
+      PKS_UNROLL for (int b = 0; b < N; ++b) p[(a * N + b) * st + i] = F[a][b];
+      p[(kc + a) * st + i] = c[a];
+      PKS_UNROLL for (int b = a; b < NF; ++b) p[(kQ + sym_index<NF>(a, b)) * st + i] = Qp[a][b];
+    }
+  }
+  // Q: the process noise covariance, N x N
+  static PKS_DEV void load_f(const R* p, size_t st, size_t i, const R* Q, R (&F)[N][N], R (&c)[N], R (&Qp)[N][N]) {
+    PKS_UNROLL for (int a = 0; a < N; ++a) {
+      PKS_UNROLL for (int b = 0; b < N; ++b) F[a][b] = a < NF ? p[(a * N + b) * st + i] : R(a == b);
+      c[a] = a < NF ? p[(kc + a) * st + i] : R(0);
+      PKS_UNROLL for (int b = a; b < N; ++b)
+        Qp[a][b] = Qp[b][a] = b < NF ? p[(kQ + sym_index<NF>(a, b)) * st + i] : Q[a * N + b];
+    }
+  }
+  static PKS_DEV void store_h(R* p, size_t st, size_t i, const R (&H)[P][N], const R (&d)[P], const R (&Rp)[P][P],
+                              const R (&yt)[P]) {
+    PKS_UNROLL for (int a = 0; a < P; ++a)
+      PKS_UNROLL for (int b = 0; b < NH; ++b) p[(kH + a * NH + b) * st + i] = H[a][b];
+    st_vec<P>(p + kd * st, st, i, d);
+    st_sym<P>(p + kR * st, st, i, Rp);
+    st_vec<P>(p + ky * st, st, i, yt);
+  }
+  static PKS_DEV void load_h(const R* p, size_t st, size_t i, R (&H)[P][N], R (&d)[P], R (&Rp)[P][P], R (&yt)[P]) {
+    PKS_UNROLL for (int a = 0; a < P; ++a)
+      PKS_UNROLL for (int b = 0; b < N; ++b) H[a][b] = b < NH ? p[(kH + a * NH + b) * st + i] : R(0);
+    ld_vec<P>(p + kd * st, st, i, d);
+    ld_sym<P>(p + kR * st, st, i, Rp);
+    ld_vec<P>(p + ky * st, st, i, yt);
+  }
 };
 
 // Where the forward kernel takes each slot's linearisation from.
@@ -243,11 +282,7 @@ PKS_DEV void transition_of(const FusedArgs& a, int64_t cs, R (&F)[Model::N][Mode
   constexpr int N = Model::N, P = Model::P;
   const size_t st = a.stride;
   if constexpr (SRC == kStoredLin) {
-    using LL = LinLayout<N, P>;
-    const R* lin = static_cast<const R*>(a.trans);
-    ld_mat<N, N>(lin + LL::kF * st, st, cs, F);
-    ld_vec<N>(lin + LL::kc * st, st, cs, c);
-    ld_sym<N>(lin + LL::kQ * st, st, cs, Qp);
+    LinRows<Model, R>::load_f(static_cast<const R*>(a.trans), st, cs, static_cast<const R*>(a.Q), F, c, Qp);
   } else {
     const Model md{static_cast<const R*>(a.params)};
     R xp[N], Pp[N][N], Qm[N][N];
@@ -300,12 +335,7 @@ PKS_DEV void filter_element_with(const FusedArgs& a, int64_t s, const R (&F)[Mod
   const int64_t cs = a.map.col(s);
   R H[P][N], d[P], Rp[P][P], yt[P];
   if constexpr (SRC == kStoredLin) {
-    using LL = LinLayout<N, P>;
-    const R* lin = static_cast<const R*>(a.trans);
-    ld_mat<P, N>(lin + LL::kH * st, st, cs, H);
-    ld_vec<P>(lin + LL::kd * st, st, cs, d);
-    ld_sym<P>(lin + LL::kR * st, st, cs, Rp);
-    ld_vec<P>(lin + LL::ky * st, st, cs, yt);
+    LinRows<Model, R>::load_h(static_cast<const R*>(a.trans), st, cs, H, d, Rp, yt);
   } else {
     const Model md{static_cast<const R*>(a.params)};
     R x[N], Px[N][N], Rm[P][P], y[P];

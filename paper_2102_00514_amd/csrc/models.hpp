@@ -29,6 +29,7 @@ template <int N_, int P_, typename R>
 struct LinearModel {
   static constexpr int N = N_, P = P_;
   static constexpr bool kAngular = false;
+  static constexpr bool kFixedRate = false;
   const R* prm;  // F (N*N), c (N), H (P*N), d (P)
 
   PKS_DEV void f(const R (&x)[N], R (&fx)[N]) const {
@@ -98,6 +99,8 @@ struct CtBearings {
   static constexpr int NT = N / 5;
   static_assert(N % 5 == 0, "coordinated-turn state is made of 5-blocks");
   static constexpr bool kAngular = true;
+  // one target: f_4(x) = x_4 and h reads x_0 and x_1 only
+  static constexpr bool kFixedRate = N == 5;
   const R* prm;  // dt, (sx, sy, target) * P
 
   PKS_DEV R dt() const { return prm[0]; }

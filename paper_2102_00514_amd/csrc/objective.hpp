@@ -142,8 +142,8 @@ struct LoglikArgs {
   const void* R;        // P x P
   const void* yslot;    // [P][stride]
   const void* traj;     // linearisation points (Taylor rows are rebuilt from them)
-  const void* trans;    // transition rows (TransLayout) of each slot; null: Taylor, rebuilt
-  const void* lin;      // optional LinLayout rows with the stored measurement linearisation
+  const void* trans;    // linearisation rows (LinRows) of each slot; null: Taylor, rebuilt
+  const void* lin;      // optional LinRows with the stored measurement linearisation
   const void* filt;     // [N + s(N)][stride] filtered moments
   SigmaRule rule;
   double* slot_ll;      // [S], slot order
@@ -153,8 +153,7 @@ struct LoglikArgs {
 template <class Model, typename R>
 __global__ __launch_bounds__(kSlotBlock) void k_loglik_slots(LoglikArgs a) {
   constexpr int N = Model::N, P = Model::P;
-  using TL = TransLayout<N>;
-  using LL = LinLayout<N, P>;
+  using Rows = LinRows<Model, R>;
   const int64_t s = a.map.slot(int64_t(blockIdx.x) * kSlotBlock + threadIdx.x);
   if (s >= a.S) return;
   if (a.flags[s] & kSlotFirst) {
@@ -165,10 +164,7 @@ __global__ __launch_bounds__(kSlotBlock) void k_loglik_slots(LoglikArgs a) {
   const int64_t cp = a.map.col(s - 1), cs = a.map.col(s);
   R F[N][N], c[N], Qp[N][N], H[P][N], d[P], Rp[P][P], yt[P];
   if (a.trans) {
-    const R* tr = static_cast<const R*>(a.trans);
-    ld_mat<N, N>(tr + TL::kF * st, st, cp, F);
-    ld_vec<N>(tr + TL::kc * st, st, cp, c);
-    ld_sym<N>(tr + TL::kQ * st, st, cp, Qp);
+    Rows::load_f(static_cast<const R*>(a.trans), st, cp, static_cast<const R*>(a.Q), F, c, Qp);
   } else {
     // Taylor transition at the linearisation point of slot k-1
     const Model md{static_cast<const R*>(a.params)};
@@ -180,11 +176,7 @@ __global__ __launch_bounds__(kSlotBlock) void k_loglik_slots(LoglikArgs a) {
     linearize_f<Model, R>(md, kTaylor, a.rule, Qm, xp, Pz, F, c, Qp);
   }
   if (a.lin) {
-    const R* lin = static_cast<const R*>(a.lin);
-    ld_mat<P, N>(lin + LL::kH * st, st, cs, H);
-    ld_vec<P>(lin + LL::kd * st, st, cs, d);
-    ld_sym<P>(lin + LL::kR * st, st, cs, Rp);
-    ld_vec<P>(lin + LL::ky * st, st, cs, yt);
+    Rows::load_h(static_cast<const R*>(a.lin), st, cs, H, d, Rp, yt);
   } else {
     const Model md{static_cast<const R*>(a.params)};
     R x[N], Px[N][N], Rm[P][P], y[P];

@@ -3,9 +3,9 @@
 // Device layout (structure of arrays, entry-major, `stride` >= slots):
 //   traj  [N + s(N)][stride]   xbar, Pbar (upper-packed) of an iterate
 //   yslot [P][stride]          y_k at the slot of x_k (unused at first slots)
-//   lin   [LinLayout::kWords][stride]   (sequential path only)
-//         transition out of the slot: F (N*N), c (N), Q' (s(N))
-//         measurement at the slot:    H (P*N), d (P), R' (s(P)), ytil (P)
+//   lin   [LinRows::kWords][stride]   (sequential path and sigma points)
+//         transition out of the slot: F, c, Q'
+//         measurement at the slot:    H, d, R', ytil
 // Slot flags: bit 0 = first slot of a track (x_0), bit 1 = last slot (x_T).
 #pragma once
 
@@ -44,7 +44,7 @@ constexpr int kSlotBlock = 256;
 template <class Model, int LIN, typename R>
 __global__ __launch_bounds__(kSlotBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_linearize(SlotArgs a) {
   constexpr int N = Model::N, P = Model::P;
-  using LL = LinLayout<N, P>;
+  using Rows = LinRows<Model, R>;
   const int64_t cs = int64_t(blockIdx.x) * kSlotBlock + threadIdx.x;
   const int64_t s = a.map.slot(cs);
   if (s >= a.S) return;
@@ -63,9 +63,7 @@ __global__ __launch_bounds__(kSlotBlock) __attribute__((amdgpu_waves_per_eu(2)))
     PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) Qm[i][j] = static_cast<const R*>(a.Q)[i * N + j];
     const bool ok = linearize_f<Model, R>(md, LIN, a.rule, Qm, xb, Pb, F, c, Qp);
     if (!ok) c[0] = quiet_nan<R>();
-    st_mat<N, N>(lin + LL::kF * st, st, cs, F);
-    st_vec<N>(lin + LL::kc * st, st, cs, c);
-    st_sym<N>(lin + LL::kQ * st, st, cs, Qp);
+    Rows::store_f(lin, st, cs, F, c, Qp);
   }
   if (!(fl & kSlotFirst)) {
     R Rm[P][P], y[P], H[P][N], d[P], Rp[P][P], yt[P];
@@ -73,10 +71,7 @@ __global__ __launch_bounds__(kSlotBlock) __attribute__((amdgpu_waves_per_eu(2)))
     ld_vec<P>(static_cast<const R*>(a.yslot), st, cs, y);
     const bool ok = linearize_h<Model, R>(md, LIN, a.rule, Rm, xb, Pb, y, H, d, Rp, yt);
     if (!ok) d[0] = quiet_nan<R>();
-    st_mat<P, N>(lin + LL::kH * st, st, cs, H);
-    st_vec<P>(lin + LL::kd * st, st, cs, d);
-    st_sym<P>(lin + LL::kR * st, st, cs, Rp);
-    st_vec<P>(lin + LL::ky * st, st, cs, yt);
+    Rows::store_h(lin, st, cs, H, d, Rp, yt);
   }
 }
 
@@ -208,9 +203,10 @@ __global__ __launch_bounds__(kSlotBlock) void k_set_mean(int64_t S, size_t strid
 // the RTS smoother over the same linearised model (the recursions the scans
 // replace).
 // ---------------------------------------------------------------------------
-template <int N, int P, typename R>
+template <class Model, typename R>
 __global__ __launch_bounds__(64) void k_sequential(SlotArgs a, const int64_t* slot_off, int ntracks) {
-  using LL = LinLayout<N, P>;
+  constexpr int N = Model::N, P = Model::P;
+  using Rows = LinRows<Model, R>;
   const int tr = blockIdx.x * 64 + threadIdx.x;
   if (tr >= ntracks) return;
   const size_t st = a.stride;
@@ -232,13 +228,8 @@ __global__ __launch_bounds__(64) void k_sequential(SlotArgs a, const int64_t* sl
   st_sym<N>(filt + N * st, st, a.map.col(s0), Pm);
   for (int64_t s = s0 + 1; s < s1; ++s) {
     R F[N][N], c[N], Qp[N][N], H[P][N], d[P], Rp[P][P], yt[P];
-    ld_mat<N, N>(lin + LL::kF * st, st, a.map.col(s - 1), F);
-    ld_vec<N>(lin + LL::kc * st, st, a.map.col(s - 1), c);
-    ld_sym<N>(lin + LL::kQ * st, st, a.map.col(s - 1), Qp);
-    ld_mat<P, N>(lin + LL::kH * st, st, a.map.col(s), H);
-    ld_vec<P>(lin + LL::kd * st, st, a.map.col(s), d);
-    ld_sym<P>(lin + LL::kR * st, st, a.map.col(s), Rp);
-    ld_vec<P>(lin + LL::ky * st, st, a.map.col(s), yt);
+    Rows::load_f(lin, st, a.map.col(s - 1), static_cast<const R*>(a.Q), F, c, Qp);
+    Rows::load_h(lin, st, a.map.col(s), H, d, Rp, yt);
     // predict
     R mp[N], Pp[N][N];
     mat_vec<N, N>(F, m, mp);
@@ -291,9 +282,7 @@ __global__ __launch_bounds__(64) void k_sequential(SlotArgs a, const int64_t* sl
   st_sym<N>(out + N * st, st, a.map.col(s1 - 1), Ps);
   for (int64_t s = s1 - 2; s >= s0; --s) {
     R F[N][N], c[N], Qp[N][N], xf[N], Pf[N][N];
-    ld_mat<N, N>(lin + LL::kF * st, st, a.map.col(s), F);
-    ld_vec<N>(lin + LL::kc * st, st, a.map.col(s), c);
-    ld_sym<N>(lin + LL::kQ * st, st, a.map.col(s), Qp);
+    Rows::load_f(lin, st, a.map.col(s), static_cast<const R*>(a.Q), F, c, Qp);
     ld_vec<N>(filt, st, a.map.col(s), xf);
     ld_sym<N>(filt + N * st, st, a.map.col(s), Pf);
     R E[N][N], g[N], L[N][N];
