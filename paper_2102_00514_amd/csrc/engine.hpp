@@ -31,6 +31,13 @@ constexpr int kScanB = 64;        // lanes per scan tile (one wavefront)
 constexpr int kLevelK = 2;        // positions per lane below the top level
 constexpr int kTopMaxK = 8;       // a single block scans at most kTopB * kTopMaxK tile aggregates
 constexpr int kTopB = 256;        // lanes of the single-block scan of the tile aggregates
+// Up to two aggregates a lane the single block is the shortest chain; past
+// that its folds, combines of whole elements by one block, cost more than the
+// two launches of a level of 64-lane blocks (2040 tiles, FP64: filtering
+// 109 us in one block, 44 us in levels; smoothing 78 and 24 us).
+// The levels need scratch: under a memory limit the single block stays as far
+// as it goes.
+constexpr int kTopOneK = 2;
 
 struct ScanLevel {
   int64_t m;
@@ -122,7 +129,7 @@ class Engine final : public EngineBase {
     tiles_ = (S + per_tile - 1) / per_tile;
     const int64_t S_pad = tiles_ * per_tile;
     stride = size_t((S_pad + 63) / 64 * 64);
-    top_single_ = tiles_ <= int64_t(kTopB) * kTopMaxK;
+    top_single_ = tiles_ <= int64_t(kTopB) * (cap ? kTopMaxK : kTopOneK);
     sched_lanes = sched_.B;
     sched_slots = sched_.K;
     sched_tiles = tiles_;

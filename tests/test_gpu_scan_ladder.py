@@ -50,3 +50,20 @@ def test_one_track(B, T):
 def test_batch(B, last):
     tracks = [wl.ct_bearings(T, seed=400 + T) for T in (250, 3, 70, last)]
     _compare(B, wl.concat_tracks(tracks, "ladder"), lin="cubature")
+
+
+@pytest.mark.parametrize("tiles", (512, 513, 2048, 2049))
+@pytest.mark.parametrize("limit", (0, 1 << 33), ids=("free", "limited"))
+def test_many_tiles(B, tiles, limit):
+    """One block over the tile aggregates, or levels of 64-lane blocks: 512 tiles
+    without a memory limit and 2048 with one are the last that one block scans."""
+    base = [wl.ct_bearings(499, seed=800 + i) for i in range(3)]
+    slots = tiles * 64 - 5
+    n = slots // 500
+    tracks = [base[i % 3] for i in range(n)]
+    if slots - 500 * n > 1:
+        tracks.append(wl.ct_bearings(slots - 500 * n - 1, seed=900))
+    pb = wl.concat_tracks(tracks, "tiles")
+    with B.Smoother(pb, n_iter=1, tile_lanes=64, lane_slots=1, max_device_bytes=limit) as sm:
+        assert sm.schedule()[2] == tiles
+    _compare(B, pb, lin="taylor", tile_lanes=64, lane_slots=1, max_device_bytes=limit)
