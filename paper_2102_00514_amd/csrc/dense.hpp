@@ -921,19 +921,6 @@ PKS_DEV void apply_f(R* cb, R* cC, const R* rA, const R* rb, const R* rC, const 
   apply_f_impl<N, R>(cb, cC, rA, rb, re, rJ, T, v1, v2, ok, [&](R*) { return rC; });
 }
 
-// The element's C stays in its record in global memory (gC, symmetric packed)
-// and is read into rJ's buffer for the last step: the element takes two LDS
-// matrices (rA, rJ).
-template <int N, typename R, typename RG>
-PKS_DEV void apply_f_lean(R* cb, R* cC, const R* rA, const R* rb, const RG* gC, const R* re, R* rJ, R* T, R* v1,
-                          R* v2, int* ok) {
-  apply_f_impl<N, R>(cb, cC, rA, rb, re, rJ, T, v1, v2, ok, [&](R* buf) {
-    ld_symm<N, N>(gC, buf);
-    wsync();
-    return static_cast<const R*>(buf);
-  });
-}
-
 // --- the smoothing operator (eq. 19) ------------------------------------------
 // l <- l (x) r in the paper's order (l earlier in time): (E_l E_r, E_l g_r + g_l, E_l L_r E_l^T + L_l).
 // T1 and T2 are scratch and may be the same matrix.
@@ -1004,32 +991,84 @@ PKS_DEV void slr(int lin, SigmaRule rule, const R* xbar, R* Pbar, Eval eval, R* 
   }
   wsync();
   // Lambda = Phi - D^T D, Phi = sum_j w_j (Z_j - zbar)(Z_j - zbar)^T
-  for (int e = lane(); e < Q * Q; e += kWave) {
-    const int a = e / Q, b = e - a * Q;
-    if (b < a) continue;
-    R s = R(0);
-    for (int j = 0; j < N; ++j)
-      s += (Zp[j * L + a] - zbar[a]) * (Zp[j * L + b] - zbar[b]) +
-           (Zm[j * L + a] - zbar[a]) * (Zm[j * L + b] - zbar[b]);
-    s = s * wj + w0 * (zc[a] - zbar[a]) * (zc[b] - zbar[b]);
-    Lam[a * L + b] = s;
-  }
-  wsync();
   const R wg = wj * gamma;
-  for (int e = lane(); e < N * Q; e += kWave) {
-    const int j = e / Q, q = e - j * Q;
-    D[j * L + q] = wg * (Zp[j * L + q] - Zm[j * L + q]);
+  auto form_D = [&] {
+    for (int e = lane(); e < N * Q; e += kWave) {
+      const int j = e / Q, q = e - j * Q;
+      D[j * L + q] = wg * (Zp[j * L + q] - Zm[j * L + q]);
+    }
+    wsync();
+  };
+  if constexpr (Q * Q > kWave && Q % 2 == 0 && (Q / 2) * (Q / 2 + 1) / 2 <= kWave) {
+    // a 2 x 2 tile of the upper triangle per lane (Q = 20: 55 tiles, one
+    // round), each entry summed in the order and with the roundings of the
+    // one-entry loops below.  With one entry per lane the two sums took seven
+    // rounds over 400 entries, half of them below the diagonal, and each
+    // operand was read from LDS for one product: the kernel, bound by its
+    // instructions, took 947 us for 65,537 slots and takes 716 us.
+    constexpr int T = Q / 2;
+    const int t = lane();
+    int ta = 0;
+    PKS_UNROLL for (int k = 1; k < T; ++k) ta += t >= k * T - k * (k - 1) / 2;
+    const bool live = t < T * (T + 1) / 2;
+    const int a0 = live ? 2 * ta : 0, b0 = live ? 2 * (t - (ta * T - ta * (ta - 1) / 2) + ta) : 0;
+    const R za[2] = {zbar[a0], zbar[a0 + 1]}, zb[2] = {zbar[b0], zbar[b0 + 1]};
+    R s[2][2] = {{R(0), R(0)}, {R(0), R(0)}};
+#pragma unroll 2
+    for (int j = 0; j < N; ++j) {
+      const R *p = Zp + j * L, *m = Zm + j * L;
+      R pa[2], pb[2], ma[2], mb[2];
+      PKS_UNROLL for (int i = 0; i < 2; ++i) {
+        pa[i] = p[a0 + i] - za[i];
+        pb[i] = p[b0 + i] - zb[i];
+        ma[i] = m[a0 + i] - za[i];
+        mb[i] = m[b0 + i] - zb[i];
+      }
+      PKS_UNROLL for (int i = 0; i < 2; ++i)
+        PKS_UNROLL for (int k = 0; k < 2; ++k) s[i][k] += fma(pa[i], pb[k], ma[i] * mb[k]);
+    }
+    PKS_UNROLL for (int i = 0; i < 2; ++i)
+      PKS_UNROLL for (int k = 0; k < 2; ++k)
+        s[i][k] = fma(w0 * (zc[a0 + i] - za[i]), zc[b0 + k] - zb[k], s[i][k] * wj);
+    wsync();
+    form_D();
+#pragma unroll 4
+    for (int j = 0; j < N; ++j) {
+      const R* d = D + j * L;
+      PKS_UNROLL for (int i = 0; i < 2; ++i) PKS_UNROLL for (int k = 0; k < 2; ++k) s[i][k] -= d[a0 + i] * d[b0 + k];
+    }
+    if (live) {
+      PKS_UNROLL for (int i = 0; i < 2; ++i)
+        PKS_UNROLL for (int k = 0; k < 2; ++k) {
+          if (i == 1 && k == 0 && a0 == b0) continue;   // below the diagonal of a diagonal tile
+          Lam[(a0 + i) * L + b0 + k] = s[i][k];
+          Lam[(b0 + k) * L + a0 + i] = s[i][k];
+        }
+    }
+    wsync();
+  } else {
+    for (int e = lane(); e < Q * Q; e += kWave) {
+      const int a = e / Q, b = e - a * Q;
+      if (b < a) continue;
+      R s = R(0);
+      for (int j = 0; j < N; ++j)
+        s += (Zp[j * L + a] - zbar[a]) * (Zp[j * L + b] - zbar[b]) +
+             (Zm[j * L + a] - zbar[a]) * (Zm[j * L + b] - zbar[b]);
+      s = s * wj + w0 * (zc[a] - zbar[a]) * (zc[b] - zbar[b]);
+      Lam[a * L + b] = s;
+    }
+    wsync();
+    form_D();
+    for (int e = lane(); e < Q * Q; e += kWave) {
+      const int a = e / Q, b = e - a * Q;
+      if (b < a) continue;
+      R s = Lam[a * L + b];
+      for (int j = 0; j < N; ++j) s -= D[j * L + a] * D[j * L + b];
+      Lam[a * L + b] = s;
+      Lam[b * L + a] = s;
+    }
+    wsync();
   }
-  wsync();
-  for (int e = lane(); e < Q * Q; e += kWave) {
-    const int a = e / Q, b = e - a * Q;
-    if (b < a) continue;
-    R s = Lam[a * L + b];
-    for (int j = 0; j < N; ++j) s -= D[j * L + a] * D[j * L + b];
-    Lam[a * L + b] = s;
-    Lam[b * L + a] = s;
-  }
-  wsync();
   bwd<N, N, Q>(Pbar, D);                    // G^T = L^-T D
   copy<N, Q, N, true>(D, G);
   for (int q = lane(); q < Q; q += kWave) {
