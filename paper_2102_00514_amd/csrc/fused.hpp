@@ -98,7 +98,16 @@ struct FusedArgs {
 // aggregates are those padding elements.
 enum : int { kTileActive = 0, kTileMixed = 1, kTileFrozen = 2 };
 
-PKS_DEV bool slot_frozen(const FusedArgs& a, int64_t s) { return a.frozen && s < a.S && a.frozen[a.track[s]]; }
+// `mixed`: the tile holds frozen and other tracks.  In any other tile that runs
+// no slot is frozen, and the two dependent loads are left out.
+PKS_DEV bool slot_frozen(const FusedArgs& a, int64_t s, bool mixed) {
+  return mixed && s < a.S && a.frozen[a.track[s]];
+}
+
+// Flags of slot s; padding slots are single-slot tracks.
+PKS_DEV unsigned slot_flags(const FusedArgs& a, int64_t s) {
+  return s < a.S ? a.flags[s] : unsigned(kSlotFirst | kSlotLast);
+}
 
 // kTileActive / kTileMixed / kTileFrozen for the slots [lo, lo + n) (tracks
 // are contiguous, so the range covers the tracks track[lo]..track[last]).
@@ -259,14 +268,15 @@ struct Form<kFormSqrt, N, R, ISO> {
   }
 };
 
-// Levenberg-Marquardt damping of the element of real slot s towards the
-// previous iterate stored in traj (the linearisation point of this iteration).
+// Levenberg-Marquardt damping of the element of real slot s (column cs)
+// towards the previous iterate stored in traj (the linearisation point of this
+// iteration).
 template <int N, typename R>
-PKS_DEV bool lm_damp_slot(const FusedArgs& a, int64_t s, typename FilterOp<N, R>::Elem& e) {
+PKS_DEV bool lm_damp_slot(const FusedArgs& a, int64_t s, int64_t cs, typename FilterOp<N, R>::Elem& e) {
   const double lam = a.lm_track ? a.lm_track[a.track[s]] : a.lm;
   if (!(lam > 0.0)) return true;
   R xb[N];
-  ld_vec<N>(static_cast<const R*>(a.traj), a.stride, a.map.col(s), xb);
+  ld_vec<N>(static_cast<const R*>(a.traj), a.stride, cs, xb);
   const bool ok = lm_damp_element<N, R>(R(lam), xb, e.A, e.b, e.C, e.eta, e.J);
   if (!ok) e.b[0] = quiet_nan<R>();
   return ok;
@@ -294,10 +304,10 @@ PKS_DEV void transition_of(const FusedArgs& a, int64_t cs, R (&F)[Model::N][Mode
   }
 }
 
-// Prior element (0, m0, P0, 0, 0) of the first slot of a track, or the
-// padding element (0, 0, I, 0, 0).
+// Prior element (0, m0, P0, 0, 0) of the first slot of a track (slot s at
+// column cs), or the padding element (0, 0, I, 0, 0).
 template <class Model, typename R, int FORM>
-PKS_DEV void prior_element(const FusedArgs& a, int64_t s, typename Form<FORM, Model::N, R, true>::FOp::Elem& e,
+PKS_DEV void prior_element(const FusedArgs& a, int64_t s, int64_t cs, typename Form<FORM, Model::N, R, true>::FOp::Elem& e,
                            bool pad = false) {
   constexpr int N = Model::N;
   using Fm = Form<FORM, N, R, true>;
@@ -316,23 +326,22 @@ PKS_DEV void prior_element(const FusedArgs& a, int64_t s, typename Form<FORM, Mo
   if constexpr (FORM == kFormCov) {
     set_zero<N>(e.J);
     Fm::prior(P0, e);
-    if (s < a.S && !pad && (a.lm > 0.0 || a.lm_track)) lm_damp_slot<N, R>(a, s, e);
+    if (s < a.S && !pad && (a.lm > 0.0 || a.lm_track)) lm_damp_slot<N, R>(a, s, cs, e);
   } else {
     set_zero<N>(e.Z);
     Fm::prior(P0, e);
   }
 }
 
-// Filtering element of slot s (not the first of its track) from the
-// surrogate transition (F, c, Q') into it.
+// Filtering element of slot s at column cs (not the first of its track) from
+// the surrogate transition (F, c, Q') into it.
 template <class Model, int SRC, typename R, int FORM>
-PKS_DEV void filter_element_with(const FusedArgs& a, int64_t s, const R (&F)[Model::N][Model::N],
+PKS_DEV void filter_element_with(const FusedArgs& a, int64_t s, int64_t cs, const R (&F)[Model::N][Model::N],
                                  const R (&c)[Model::N], const R (&Qp)[Model::N][Model::N],
                                  typename Form<FORM, Model::N, R, true>::FOp::Elem& e) {
   constexpr int N = Model::N, P = Model::P;
   using Fm = Form<FORM, N, R, true>;
   const size_t st = a.stride;
-  const int64_t cs = a.map.col(s);
   R H[P][N], d[P], Rp[P][P], yt[P];
   if constexpr (SRC == kStoredLin) {
     LinRows<Model, R>::load_h(static_cast<const R*>(a.trans), st, cs, H, d, Rp, yt);
@@ -348,25 +357,33 @@ PKS_DEV void filter_element_with(const FusedArgs& a, int64_t s, const R (&F)[Mod
   }
   bool ok = Fm::template element<P>(F, c, Qp, H, d, Rp, yt, e);
   if constexpr (FORM == kFormCov) {
-    if (a.lm > 0.0 || a.lm_track) ok = lm_damp_slot<N, R>(a, s, e) && ok;
+    if (a.lm > 0.0 || a.lm_track) ok = lm_damp_slot<N, R>(a, s, cs, e) && ok;
   }
   if (!ok) e.b[0] = quiet_nan<R>();
 }
 
-// Filtering element of slot s.
+// Column of the slot before a lane's first one (lane l of a tile whose columns
+// start at c0): the last slot of the lane before, or the tile's predecessor's
+// last column.  Spelt out because SlotMap::col divides (64 bit: 140
+// instructions, three times a slot in the walks below).
+PKS_DEV int64_t col_before(const FusedArgs& a, int64_t c0, int lane, int B) {
+  return c0 - 1 + (lane > 0 ? lane + int64_t(a.K - 1) * B : 0);
+}
+
+// Filtering element of slot s at column cs (flags fl), whose predecessor is at
+// column cp.
 template <class Model, int SRC, typename R, int FORM = kFormCov>
-PKS_DEV void build_filter_element(const FusedArgs& a, int64_t s,
+PKS_DEV void build_filter_element(const FusedArgs& a, int64_t s, int64_t cs, int64_t cp, unsigned fl, bool mixed,
                                   typename Form<FORM, Model::N, R, true>::FOp::Elem& e) {
   constexpr int N = Model::N;
-  const unsigned fl = s < a.S ? a.flags[s] : (kSlotFirst | kSlotLast);
-  const bool fz = slot_frozen(a, s);
+  const bool fz = slot_frozen(a, s, mixed);
   if ((fl & kSlotFirst) || fz) {
-    prior_element<Model, R, FORM>(a, s, e, fz);
+    prior_element<Model, R, FORM>(a, s, cs, e, fz);
     return;
   }
   R F[N][N], c[N], Qp[N][N];
-  transition_of<Model, SRC, R>(a, a.map.col(s - 1), F, c, Qp);
-  filter_element_with<Model, SRC, R, FORM>(a, s, F, c, Qp, e);
+  transition_of<Model, SRC, R>(a, cp, F, c, Qp);
+  filter_element_with<Model, SRC, R, FORM>(a, s, cs, F, c, Qp, e);
 }
 
 // A lane's walk over its K slots in a forward down-sweep (K > 1): the
@@ -375,23 +392,25 @@ PKS_DEV void build_filter_element(const FusedArgs& a, int64_t s,
 // each slot is kept for the next slot's element and handed to `visit` with
 // the slot's filtered carry: visit(j, s, cs, carry, flags, F, c, Q').
 template <class Model, int SRC, typename R, bool ISO, int FORM, class Visit>
-PKS_DEV void walk_lane(const FusedArgs& a, int64_t base, int64_t cbase, int B,
+PKS_DEV void walk_lane(const FusedArgs& a, int64_t base, int64_t c0, int lane, int B, bool mixed,
                        typename Form<FORM, Model::N, R, ISO>::FOp::Carry& c, bool have, Visit&& visit) {
   constexpr int N = Model::N;
   using FOp = typename Form<FORM, N, R, ISO>::FOp;
   R Ft[N][N], ct[N], Qt[N][N];   // transition into the current slot, then out of it
   bool trans_ok = false;
+  unsigned next = slot_flags(a, base);
   for (int j = 0; j < a.K; ++j) {
-    const int64_t s = base + j, cs = cbase + int64_t(j) * B;
-    unsigned fl = s < a.S ? a.flags[s] : (kSlotFirst | kSlotLast);
-    if (slot_frozen(a, s)) fl = kSlotFirst | kSlotLast | kSlotFrozen;
+    const int64_t s = base + j, cs = c0 + lane + int64_t(j) * B;
+    unsigned fl = next;
+    if (j + 1 < a.K) next = slot_flags(a, s + 1);   // a slot ahead of its use
+    if (slot_frozen(a, s, mixed)) fl = kSlotFirst | kSlotLast | kSlotFrozen;
     if (a.K > 1) {
       typename Form<FORM, N, R, true>::FOp::Elem e;
       if (fl & kSlotFirst) {
-        prior_element<Model, R, FORM>(a, s, e, (fl & kSlotFrozen) != 0);
+        prior_element<Model, R, FORM>(a, s, cs, e, (fl & kSlotFrozen) != 0);
       } else {
-        if (!trans_ok) transition_of<Model, SRC, R>(a, a.map.col(s - 1), Ft, ct, Qt);
-        filter_element_with<Model, SRC, R, FORM>(a, s, Ft, ct, Qt, e);
+        if (!trans_ok) transition_of<Model, SRC, R>(a, j > 0 ? cs - B : col_before(a, c0, lane, B), Ft, ct, Qt);
+        filter_element_with<Model, SRC, R, FORM>(a, s, cs, Ft, ct, Qt, e);
       }
       if (have) {
         typename FOp::Carry n;
@@ -415,18 +434,20 @@ __global__ __launch_bounds__(B) void k_forward_up(FusedArgs a) {
   const int lane = threadIdx.x;
   const int64_t tile = blockIdx.x;
   const int64_t base = (tile * B + lane) * a.K;
-  const int64_t cbase = tile * B * a.K + lane;   // column of slot base + j: cbase + j * B
+  const int64_t c0 = tile * B * a.K;   // column of slot base + j: c0 + lane + j * B
   if (tile == 0)
     for (int i = lane; i <= a.ntracks; i += B) a.delta_bits[i] = 0ull;
+  bool mixed = false;
   if (a.frozen) {
     __shared__ int s_state;
     if (lane == 0) s_state = tile_freeze_state(a, tile * B * a.K, int64_t(B) * a.K);
     __syncthreads();
+    mixed = s_state == kTileMixed;
     if (s_state == kTileFrozen) {
       // the tile's aggregate is the padding element; nothing else is read
       if (lane == B - 1) {
         typename Op::Elem e;
-        prior_element<Model, R, FORM>(a, a.S, e, true);
+        prior_element<Model, R, FORM>(a, a.S, 0, e, true);
         Op::store(static_cast<R*>(a.ta_f), size_t(a.tiles), tile, e);
       }
       return;
@@ -437,14 +458,19 @@ __global__ __launch_bounds__(B) void k_forward_up(FusedArgs a) {
   // which is also their tile's aggregate, and stay out of the ladder
   const int live = a.K == 1 ? wave_positions<B>(a.S, tile, lane, 1) : 64;
   if (live == 0) {
-    prior_element<Model, R, FORM>(a, a.S, acc, true);
+    prior_element<Model, R, FORM>(a, a.S, 0, acc, true);
   } else {
     // each lane folds its K elements as they are built; the down-sweep builds
     // them again rather than reading them back
-    build_filter_element<Model, SRC, R, FORM>(a, base, acc);
+    const unsigned first = slot_flags(a, base);
+    unsigned next = a.K > 1 ? slot_flags(a, base + 1) : 0u;
+    build_filter_element<Model, SRC, R, FORM>(a, base, c0 + lane, col_before(a, c0, lane, B), first, mixed, acc);
     for (int j = 1; j < a.K; ++j) {
       typename Op::Elem e, r;
-      build_filter_element<Model, SRC, R, FORM>(a, base + j, e);
+      const int64_t cs = c0 + lane + int64_t(j) * B;
+      const unsigned fl = next;
+      if (j + 1 < a.K) next = slot_flags(a, base + j + 1);   // a slot ahead of its use
+      build_filter_element<Model, SRC, R, FORM>(a, base + j, cs, cs - B, fl, mixed, e);
       Op::combine(acc, e, r);
       acc = r;
     }
@@ -500,17 +526,19 @@ __global__ __launch_bounds__(B) void k_forward_down_backward_up(FusedArgs a) {
   const size_t st = a.stride;
   const int rl = B - 1 - lane;
   const int64_t rt = a.tiles - 1 - tile;
+  bool mixed = false;
   if (a.frozen) {
     __shared__ int s_state;
     if (lane == 0) s_state = tile_freeze_state(a, tile * B * a.K, int64_t(B) * a.K);
     __syncthreads();
+    mixed = s_state == kTileMixed;
     if (s_state == kTileFrozen) {
       if (rl == B - 1) {
         typename SOp::Elem se;
         typename FOp::Carry pc;
         set_zero<N>(pc.b);
         typename FOp::Elem pe;
-        prior_element<Model, R, FORM>(a, a.S, pe, true);
+        prior_element<Model, R, FORM>(a, a.S, 0, pe, true);
         FOp::to_carry(pe, pc);
         Fm::last(pc, se);
         SOp::store(static_cast<R*>(a.ta_s), size_t(a.tiles), rt, se);
@@ -529,9 +557,8 @@ __global__ __launch_bounds__(B) void k_forward_down_backward_up(FusedArgs a) {
     typename FOp::Carry c;
     bool have;
     lane_filter_carry<N, B, R, ISO, FORM>(a, tile, lane, c, have);
-    const int64_t cbase = tile * B * a.K + lane;
     walk_lane<Model, SRC, R, ISO, FORM>(
-        a, base, cbase, B, c, have,
+        a, base, tile * B * a.K, lane, B, mixed, c, have,
         [&](int j, int64_t s, int64_t cs, const typename FOp::Carry& cj, unsigned fl, R(&F)[N][N], R(&cc)[N],
             R(&Qp)[N][N]) {
           if (a.filt && !(fl & kSlotFrozen)) Fm::store_moments(static_cast<R*>(a.filt), st, cs, cj);
@@ -541,7 +568,7 @@ __global__ __launch_bounds__(B) void k_forward_down_backward_up(FusedArgs a) {
             // padding end element (0, 0, I) in place of the frozen slot's
             typename FOp::Elem pe;
             typename FOp::Carry pc;
-            prior_element<Model, R, FORM>(a, a.S, pe, true);
+            prior_element<Model, R, FORM>(a, a.S, 0, pe, true);
             FOp::to_carry(pe, pc);
             Fm::last(pc, se);
           } else if (fl & kSlotLast) {
@@ -589,8 +616,7 @@ __global__ __launch_bounds__(B) void k_forward_down_filter(FusedArgs a) {
   typename FOp::Carry c;
   bool have;
   lane_filter_carry<N, B, R, ISO, FORM>(a, tile, lane, c, have);
-  const int64_t cbase = tile * B * a.K + lane;
-  walk_lane<Model, SRC, R, ISO, FORM>(a, base, cbase, B, c, have,
+  walk_lane<Model, SRC, R, ISO, FORM>(a, base, tile * B * a.K, lane, B, a.frozen != nullptr, c, have,
                                       [&](int, int64_t, int64_t cs, const typename FOp::Carry& cj, unsigned,
                                           R(&)[N][N], R(&)[N], R(&)[N][N]) {
                                         Fm::store_moments(static_cast<R*>(a.filt), a.stride, cs, cj);
@@ -682,7 +708,7 @@ __global__ __launch_bounds__(B) void k_backward_down(FusedArgs a) {
         have = true;
       }
     }
-    if (s < a.S && !slot_frozen(a, s)) {
+    if (s < a.S && !slot_frozen(a, s, s_state == kTileMixed)) {
       double m = 0.0;
       bool nan = false;
       PKS_UNROLL for (int i = 0; i < N; ++i) {
