@@ -36,7 +36,8 @@ constexpr int kTopB = 256;        // lanes of the single-block scan of the tile 
 // two launches of a level of 64-lane blocks (2040 tiles, FP64: filtering
 // 109 us in one block, 44 us in levels; smoothing 78 and 24 us).
 // The levels need scratch: under a memory limit the single block stays as far
-// as it goes.
+// as it goes; so it does in FP32, whose results move with the shape of the
+// tree, and in the square-root form, where the gain has not been measured.
 constexpr int kTopOneK = 2;
 
 struct ScanLevel {
@@ -129,7 +130,7 @@ class Engine final : public EngineBase {
     tiles_ = (S + per_tile - 1) / per_tile;
     const int64_t S_pad = tiles_ * per_tile;
     stride = size_t((S_pad + 63) / 64 * 64);
-    top_single_ = tiles_ <= int64_t(kTopB) * (cap ? kTopMaxK : kTopOneK);
+    top_single_ = tiles_ <= int64_t(kTopB) * (cap || sizeof(R) == 4 || form_ == SM_FORM_SQRT ? kTopMaxK : kTopOneK);
     sched_lanes = sched_.B;
     sched_slots = sched_.K;
     sched_tiles = tiles_;
