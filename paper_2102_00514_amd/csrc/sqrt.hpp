@@ -70,12 +70,57 @@ PKS_DEV void tria(R (&X)[M][K], R (&L)[M][M]) {
   }
 }
 
-// X (M x K) = [A, B] for A (M x K1), B (M x K2), K = K1 + K2.
-template <int M, int K1, int K2, typename R>
-PKS_DEV void hcat(const R (&A)[M][K1], const R (&B)[M][K2], R (&X)[M][K1 + K2]) {
-  PKS_UNROLL for (int i = 0; i < M; ++i) {
-    PKS_UNROLL for (int j = 0; j < K1; ++j) X[i][j] = A[i][j];
-    PKS_UNROLL for (int j = 0; j < K2; ++j) X[i][K1 + j] = B[i][j];
+// tria of [X, T] for X (M x M) and a lower-triangular T: the same reflections
+// without the products with T's zeros.  Row r of T is zero past column r, and
+// stays so: rows only receive multiples of earlier ones.  M + 1 columns a
+// reflection instead of 2 M - r (n = 5: 150 multiply-adds instead of 220, and
+// ten words fewer to hold).  X and T are destroyed.
+template <int M, typename R>
+PKS_DEV void tria_lower(R (&X)[M][M], R (&T)[M][M], R (&L)[M][M]) {
+  R D[M][M];
+  PKS_UNROLL for (int r = 0; r < M; ++r) {
+    R ss = R(0);
+    PKS_UNROLL for (int j = r; j < M; ++j) ss += X[r][j] * X[r][j];
+    PKS_UNROLL for (int j = 0; j <= r; ++j) ss += T[r][j] * T[r][j];
+    const bool nz = ss > R(0);
+    const R inv = rsqrt_nr(nz ? ss : R(1));
+    const R nrm = nz ? ss * inv : R(0);
+    const R x0 = X[r][r];
+    const R sg = x0 < R(0) ? R(-1) : R(1);
+    const R v0 = x0 + sg * nrm;
+    const R den = nrm * (nrm + sg * x0);
+    const R beta = nz ? rcp_nr(den > R(0) ? den : R(1)) : R(0);
+    PKS_UNROLL for (int i = r + 1; i < M; ++i) {
+      R dot = X[i][r] * v0;
+      PKS_UNROLL for (int j = r + 1; j < M; ++j) dot += X[i][j] * X[r][j];
+      PKS_UNROLL for (int j = 0; j <= r; ++j) dot += T[i][j] * T[r][j];
+      const R f = beta * dot;
+      X[i][r] -= f * v0;
+      PKS_UNROLL for (int j = r + 1; j < M; ++j) X[i][j] -= f * X[r][j];
+      PKS_UNROLL for (int j = 0; j <= r; ++j) T[i][j] -= f * T[r][j];
+    }
+    D[r][r] = nrm;
+    PKS_UNROLL for (int i = r + 1; i < M; ++i) D[i][r] = -sg * X[i][r];
+    PKS_UNROLL for (int j = r + 1; j < M; ++j) D[r][j] = R(0);
+  }
+  PKS_UNROLL for (int i = 0; i < M; ++i) PKS_UNROLL for (int j = 0; j < M; ++j) L[i][j] = D[i][j];
+}
+
+// L = tria([X, T]), T lower triangular.  FP32 keeps the general form.
+template <int N, typename R>
+PKS_DEV void tria_cat(R (&X)[N][N], const R (&T)[N][N], R (&L)[N][N]) {
+  if constexpr (sizeof(R) == 8) {
+    R D[N][N];
+    PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) D[i][j] = T[i][j];
+    tria_lower<N>(X, D, L);
+  } else {
+    R Y[N][2 * N];
+    PKS_UNROLL for (int i = 0; i < N; ++i)
+      PKS_UNROLL for (int j = 0; j < N; ++j) {
+        Y[i][j] = X[i][j];
+        Y[i][N + j] = T[i][j];
+      }
+    tria<N, 2 * N>(Y, L);
   }
 }
 
@@ -196,7 +241,8 @@ struct SqrtFilterCarry {
 
 template <int N, typename R, bool kIsolate = true>
 struct SqrtFilterOp {
-  static constexpr bool kInLds = false;
+  // FP64: the wavefront ladder keeps the elements in LDS (combine_at)
+  static constexpr bool kInLds = sizeof(R) == 8;
   // the scan ladders keep one copy of the operator instead of unrolling it
   static constexpr bool kCompact = true;
   using Elem = SqrtFilterElem<N, R>;
@@ -254,13 +300,13 @@ struct SqrtFilterOp {
         PKS_UNROLL for (int t = (i > j ? i : j); t < N; ++t) s += U[t][i] * Zj[t][j];
         B[i][j] = s;
       }
-    R X[N][2 * N], Xi[N][N];
+    R X[N][N], Id[N][N], Xi[N][N];
     PKS_UNROLL for (int i = 0; i < N; ++i)
       PKS_UNROLL for (int j = 0; j < N; ++j) {
         X[i][j] = B[i][j];
-        X[i][N + j] = R(i == j);
+        Id[i][j] = R(i == j);
       }
-    tria<N, 2 * N>(X, Xi);
+    tria_cat<N>(X, Id, Xi);
     // W^T = Xi^-1 U^T
     R Wt[N][N];
     PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) Wt[i][j] = U[j][i];
@@ -282,20 +328,66 @@ struct SqrtFilterOp {
     PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) B[i][j] = BZ[i][j];
   }
 
+  // Xi22 = Zj Phi^-T with Phi = tria([B^T, I]), B = Ui^T Zj
+  static PKS_DEV void factor22(const R (&U)[N][N], const R (&Z)[N][N], R (&X22)[N][N]) {
+    R X[N][N], Id[N][N], Phi[N][N];
+    PKS_UNROLL for (int i = 0; i < N; ++i)
+      PKS_UNROLL for (int j = 0; j < N; ++j) {
+        R s = R(0);   // (B^T)[i][j] = B[j][i] = sum_t U[t][j] Z[t][i]
+        PKS_UNROLL for (int t = (i > j ? i : j); t < N; ++t) s += U[t][j] * Z[t][i];
+        X[i][j] = s;
+        Id[i][j] = R(i == j);
+      }
+    tria_cat<N>(X, Id, Phi);
+    // X22^T = Phi^-1 Zj^T
+    R T[N][N];
+    PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) T[i][j] = Z[j][i];
+    tril_solve<N, N>(Phi, T);
+    PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) X22[i][j] = T[j][i];
+  }
+
   // bo = A_j (b + W (W^T eta_j - V b)) + b_j
-  static PKS_DEV void mean_update(const R (&b)[N], const Elem& r, const R (&V)[N][N], const R (&W)[N][N],
-                                  R (&bo)[N]) {
+  static PKS_DEV void mean_update(const R (&b)[N], const R (&Aj)[N][N], const R (&bj)[N], const R (&ej)[N],
+                                  const R (&V)[N][N], const R (&W)[N][N], R (&bo)[N]) {
     R u[N], vb[N], t[N];
-    mat_tvec<N, N>(W, r.eta, u);
+    mat_tvec<N, N>(W, ej, u);
     mat_vec<N, N>(V, b, vb);
     PKS_UNROLL for (int i = 0; i < N; ++i) u[i] -= vb[i];
     mat_vec<N, N>(W, u, t);
     PKS_UNROLL for (int i = 0; i < N; ++i) t[i] += b[i];
     PKS_UNROLL for (int i = 0; i < N; ++i) {
-      R s = r.b[i];
-      PKS_UNROLL for (int k = 0; k < N; ++k) s += r.A[i][k] * t[k];
+      R s = bj[i];
+      PKS_UNROLL for (int k = 0; k < N; ++k) s += Aj[i][k] * t[k];
       bo[i] = s;
     }
+  }
+  // eta_ij = A_i^T (s - V^T (W^T s)) + eta_i,  s = eta_j - Z_j (Z_j^T b_i)
+  static PKS_DEV void info_mean(const R (&b)[N], const R (&Zj)[N][N], const R (&ej)[N], const R (&V)[N][N],
+                                const R (&W)[N][N], R (&s)[N]) {
+    R z[N], ws[N], vw[N];
+    mat_tvec<N, N>(Zj, b, z);
+    mat_vec<N, N>(Zj, z, s);
+    PKS_UNROLL for (int i = 0; i < N; ++i) s[i] = ej[i] - s[i];
+    mat_tvec<N, N>(W, s, ws);
+    mat_tvec<N, N>(V, ws, vw);
+    PKS_UNROLL for (int i = 0; i < N; ++i) s[i] -= vw[i];
+  }
+  // U_ij = tria([A_j W, U_j])
+  static PKS_DEV void join_U(const R (&Aj)[N][N], const R (&W)[N][N], const R (&Uj)[N][N], R (&o)[N][N]) {
+    R AW[N][N];
+    mat_mul<N, N, N>(Aj, W, AW);
+    tria_cat<N>(AW, Uj, o);
+  }
+  // Z_ij = tria([A_i^T Xi22, Z_i])
+  static PKS_DEV void join_Z(const R (&Ai)[N][N], const R (&X22)[N][N], const R (&Zi)[N][N], R (&o)[N][N]) {
+    R AX[N][N];
+    PKS_UNROLL for (int i = 0; i < N; ++i)
+      PKS_UNROLL for (int j = 0; j < N; ++j) {
+        R s = R(0);
+        PKS_UNROLL for (int t = 0; t < N; ++t) s += Ai[t][i] * X22[t][j];
+        AX[i][j] = s;
+      }
+    tria_cat<N>(AX, Zi, o);
   }
 
   // out = l (x) r
@@ -304,24 +396,8 @@ struct SqrtFilterOp {
       o = r;
       return;
     }
-    // Xi22 = Zj Phi^-T with Phi = tria([B^T, I]), B = Ui^T Zj
     R X22[N][N];
-    {
-      R X[N][2 * N], Phi[N][N];
-      PKS_UNROLL for (int i = 0; i < N; ++i)
-        PKS_UNROLL for (int j = 0; j < N; ++j) {
-          R s = R(0);   // (B^T)[i][j] = B[j][i] = sum_t U[t][j] Z[t][i]
-          PKS_UNROLL for (int t = (i > j ? i : j); t < N; ++t) s += l.U[t][j] * r.Z[t][i];
-          X[i][j] = s;
-          X[i][N + j] = R(i == j);
-        }
-      tria<N, 2 * N>(X, Phi);
-      // X22^T = Phi^-1 Zj^T
-      R T[N][N];
-      PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) T[i][j] = r.Z[j][i];
-      tril_solve<N, N>(Phi, T);
-      PKS_UNROLL for (int i = 0; i < N; ++i) PKS_UNROLL for (int j = 0; j < N; ++j) X22[i][j] = T[j][i];
-    }
+    factor22(l.U, r.Z, X22);
     R V[N][N], W[N][N];
     core(l.U, r.Z, V, W);
     // A_ij = A_j (A_i - W (V A_i))
@@ -334,38 +410,75 @@ struct SqrtFilterOp {
     }
     // b_ij = A_j (b_i + W (W^T eta_j - V b_i)) + b_j: (I + C_i J_j)^-1 (b_i + C_i eta_j)
     // = (I - W V) b_i + W W^T eta_j, with no large intermediate to cancel
-    mean_update(l.b, r, V, W, o.b);
-    // eta_ij = A_i^T (s - V^T (W^T s)) + eta_i,  s = eta_j - Z_j (Z_j^T b_i)
-    {
-      R z[N], s[N], ws[N], vw[N];
-      mat_tvec<N, N>(r.Z, l.b, z);
-      mat_vec<N, N>(r.Z, z, s);
-      PKS_UNROLL for (int i = 0; i < N; ++i) s[i] = r.eta[i] - s[i];
-      mat_tvec<N, N>(W, s, ws);
-      mat_tvec<N, N>(V, ws, vw);
-      PKS_UNROLL for (int i = 0; i < N; ++i) s[i] -= vw[i];
-      mat_tvec<N, N>(l.A, s, z);
-      PKS_UNROLL for (int i = 0; i < N; ++i) o.eta[i] = z[i] + l.eta[i];
+    mean_update(l.b, r.A, r.b, r.eta, V, W, o.b);
+    R sv[N], z[N];
+    info_mean(l.b, r.Z, r.eta, V, W, sv);
+    mat_tvec<N, N>(l.A, sv, z);
+    PKS_UNROLL for (int i = 0; i < N; ++i) o.eta[i] = z[i] + l.eta[i];
+    join_U(r.A, W, r.U, o.U);
+    join_Z(l.A, X22, l.Z, o.Z);
+  }
+
+  // combine on elements kept in LDS, as FilterOp::combine_at.  Both operands
+  // and the factors do not fit the registers (748 bytes a lane went to
+  // scratch, 13 us a combine at n = 5; T = 8191, top scan of 127 tiles: 94 us
+  // before, 64 us now; forward_up 77 us before, 53 us now), so each block is
+  // read where it is used.
+  static PKS_DEV void combine_at(R* p, size_t i, const R* lp, size_t li) {
+    constexpr size_t st = 64;
+    R *pA = p, *pb = p + N * N * st, *pU = pb + N * st, *pe = pU + kS * st, *pZ = pe + N * st;
+    const R *lA = lp, *lb = lp + N * N * st, *lU = lb + N * st, *le = lU + kS * st, *lZ = le + N * st;
+    R A[N][N], V[N][N], W[N][N], b[N], e[N], v[N], s[N];
+    if constexpr (kIsolate) {
+      ld_mat<N, N>(pA, st, i, A);
+      if (restarts(A)) return;
+      order_lds();
     }
-    // U_ij = tria([A_j W, U_j])
     {
-      R AW[N][N], X[N][2 * N];
-      mat_mul<N, N, N>(r.A, W, AW);
-      hcat<N, N, N>(AW, r.U, X);
-      tria<N, 2 * N>(X, o.U);
+      R U[N][N], Z[N][N];
+      ld_tril<N>(lU, st, li, U);
+      ld_tril<N>(pZ, st, i, Z);
+      core(U, Z, V, W);
+      order_lds();
+      ld_vec<N>(lb, st, li, b);
+      ld_vec<N>(pe, st, i, e);
+      info_mean(b, Z, e, V, W, s);
     }
-    // Z_ij = tria([A_i^T Xi22, Z_i])
+    ld_mat<N, N>(pA, st, i, A);
+    ld_vec<N>(pb, st, i, v);
+    mean_update(b, A, v, e, V, W, b);
+    st_vec<N>(pb, st, i, b);
+    R Ai[N][N], T[N][N];
+    ld_mat<N, N>(lA, st, li, Ai);
+    // A_ij = A_j (A_i - W (V A_i))
     {
-      R AX[N][N], X[N][2 * N];
-      PKS_UNROLL for (int i = 0; i < N; ++i)
-        PKS_UNROLL for (int j = 0; j < N; ++j) {
-          R s = R(0);
-          PKS_UNROLL for (int t = 0; t < N; ++t) s += l.A[t][i] * X22[t][j];
-          AX[i][j] = s;
-        }
-      hcat<N, N, N>(AX, l.Z, X);
-      tria<N, 2 * N>(X, o.Z);
+      R VA[N][N];
+      mat_mul<N, N, N>(V, Ai, VA);
+      mat_mul<N, N, N>(W, VA, T);
+      PKS_UNROLL for (int a = 0; a < N; ++a) PKS_UNROLL for (int c = 0; c < N; ++c) T[a][c] = Ai[a][c] - T[a][c];
+      mat_mul<N, N, N>(A, T, V);
+      st_mat<N, N>(pA, st, i, V);
     }
+    mat_tvec<N, N>(Ai, s, v);
+    ld_vec<N>(le, st, li, e);
+    PKS_UNROLL for (int a = 0; a < N; ++a) v[a] += e[a];
+    st_vec<N>(pe, st, i, v);
+    order_lds();
+    // Xi22 from lU and pZ, neither of them written yet
+    {
+      R U[N][N], Z[N][N];
+      ld_tril<N>(lU, st, li, U);
+      ld_tril<N>(pZ, st, i, Z);
+      factor22(U, Z, V);
+      order_lds();
+      ld_tril<N>(lZ, st, li, Z);
+      join_Z(Ai, V, Z, T);
+      st_tril<N>(pZ, st, i, T);
+    }
+    order_lds();
+    ld_tril<N>(pU, st, i, V);
+    join_U(A, W, V, T);
+    st_tril<N>(pU, st, i, T);
   }
 
   // out = c (x) r for a carry c
@@ -379,11 +492,8 @@ struct SqrtFilterOp {
     }
     R V[N][N], W[N][N];
     core(c.U, r.Z, V, W);
-    mean_update(c.b, r, V, W, o.b);
-    R AW[N][N], X[N][2 * N];
-    mat_mul<N, N, N>(r.A, W, AW);
-    hcat<N, N, N>(AW, r.U, X);
-    tria<N, 2 * N>(X, o.U);
+    mean_update(c.b, r.A, r.b, r.eta, V, W, o.b);
+    join_U(r.A, W, r.U, o.U);
   }
 };
 
@@ -462,10 +572,9 @@ struct SqrtSmootherOp {
       PKS_UNROLL for (int t = 0; t < N; ++t) s += y.E[i][t] * x.g[t];
       o.g[i] = s;
     }
-    R ED[N][N], X[N][2 * N];
+    R ED[N][N];
     mat_mul<N, N, N>(y.E, x.D, ED);
-    hcat<N, N, N>(ED, y.D, X);
-    tria<N, 2 * N>(X, o.D);
+    tria_cat<N>(ED, y.D, o.D);
   }
   static PKS_DEV void apply(const Carry& c, const Elem& y, Carry& o) {
     if (restarts(y.E)) {
@@ -480,10 +589,9 @@ struct SqrtSmootherOp {
       PKS_UNROLL for (int t = 0; t < N; ++t) s += y.E[i][t] * c.g[t];
       o.g[i] = s;
     }
-    R ED[N][N], X[N][2 * N];
+    R ED[N][N];
     mat_mul<N, N, N>(y.E, c.D, ED);
-    hcat<N, N, N>(ED, y.D, X);
-    tria<N, 2 * N>(X, o.D);
+    tria_cat<N>(ED, y.D, o.D);
   }
 };
 

@@ -67,3 +67,15 @@ def test_many_tiles(B, tiles, limit):
     with B.Smoother(pb, n_iter=1, tile_lanes=64, lane_slots=1, max_device_bytes=limit) as sm:
         assert sm.schedule()[2] == tiles
     _compare(B, pb, lin="taylor", tile_lanes=64, lane_slots=1, max_device_bytes=limit)
+
+
+@pytest.mark.parametrize("T", (1, 15, 16, 17, 62, 63, 64, 127, 300, 64 * 64, 64 * 256, 64 * 257))
+def test_square_root_form(B, T):
+    """The square-root operator on elements in LDS: edges of rows and wavefronts,
+    and top scans of one slot a lane (256 tiles) and of two (257)."""
+    pb = wl.ct_bearings(T, seed=1000 + T)
+    m, c = _run(B, pb, lin="taylor", form="sqrt")
+    ms, cs = _run(B, pb, lin="taylor")
+    for got, want in ((m, ms), (c.reshape(len(m), -1), cs.reshape(len(m), -1))):
+        scale = np.abs(want).max(axis=0)
+        assert np.all(np.abs(got - want) <= TOL * scale)
