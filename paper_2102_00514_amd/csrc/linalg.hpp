@@ -249,8 +249,10 @@ PKS_DEV void st_sym(R* __restrict__ base, size_t stride, size_t s, const R (&A)[
 // LDS accesses on the two sides of this point stay in their order (no
 // instruction: a wavefront's LDS accesses are executed in program order).
 PKS_DEV void order_lds() {
+#if defined(__HIP_DEVICE_COMPILE__)   // a host build of the per-lane algebra has no lanes to order
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+#endif
 }
 
 }  // namespace pks
