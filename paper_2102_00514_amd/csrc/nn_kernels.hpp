@@ -9,10 +9,10 @@
 
 #include <cstdint>
 
+#include "wgrad_chunks.hpp"
+
 namespace wsn {
 
-constexpr int kTile = 64;     // output rows and columns per block
-constexpr int kTk = 16;       // reduction depth staged per LDS step
 constexpr int kThreads = 256; // 16 x 16 threads, 4 x 4 outputs each
 constexpr int kPad = 4;       // LDS row padding: column writes of 16 rows hit distinct banks
 
@@ -198,7 +198,6 @@ __global__ __launch_bounds__(256) void k_pack_direct(PackDirectArgs args) {
   }
 }
 
-constexpr int kDirP = 64;    // most positions per block
 constexpr int kDirC = 128;   // source channels per stage
 
 template <int KT, int EPI, int PW>

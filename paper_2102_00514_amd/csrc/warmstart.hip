@@ -56,9 +56,6 @@ int64_t total_params(const std::vector<LayerSpec>& L) { return L.back().b_off + 
 
 std::string hip_msg(hipError_t e, const char* what) { return std::string(what) + ": " + hipGetErrorString(e); }
 
-constexpr int kWgradTarget = 512;  // blocks aimed at per weight-gradient launch
-constexpr int kDirectTarget = 512; // the same for the matrix-core form (two blocks per CU)
-
 }  // namespace
 
 struct ws_net {
@@ -112,23 +109,6 @@ struct ws_net {
 
   wsn::WindowTable table() const { return {win_track, win_start, meas_off, first}; }
 
-  // Chunks of the weight-gradient reduction for M x (Kr + 1) tiles over N
-  // positions.  The result never exceeds wgrad_chunk_bound(M, Kr, N), which
-  // grows with N, so a workspace sized by the bound at max_batch serves every batch.
-  static int wgrad_chunk_bound(int M, int Kr, int N) {
-    const int tiles = ((Kr + 1 + wsn::kTile - 1) / wsn::kTile) * ((M + wsn::kTile - 1) / wsn::kTile);
-    return std::max(1, std::min((kWgradTarget + tiles - 1) / tiles, (N + wsn::kTile - 1) / wsn::kTile));
-  }
-
-  static int wgrad_chunks(int M, int Kr, int N, int* chunk) {
-    int chunks = wgrad_chunk_bound(M, Kr, N);
-    int c = (N + chunks - 1) / chunks;
-    c = (c + wsn::kTk - 1) / wsn::kTk * wsn::kTk;
-    chunks = (N + c - 1) / c;
-    *chunk = c;
-    return chunks;
-  }
-
   ws_status setup(const ws_config& c, hipStream_t s) {
     cfg = c;
     stream = s;
@@ -159,10 +139,11 @@ struct ws_net {
       A_(&dh[i], size_t(c.width) * pos);
       A_(&dz[i], size_t(c.width) * pos);
     }
+    // bounds, not the chunks of max_batch: smaller batches may have more (wgrad_chunks.hpp)
     for (const auto& L : layers) {
       const int Kr = L.cin * L.K;
-      int c_;
-      const int chunks = direct(L) ? direct_chunk(L, int(pos), &c_) : wgrad_chunk_bound(L.cout, Kr, int(pos));
+      const int chunks =
+          direct(L) ? wsn::direct_bound(L.cout, wgrad_channels(L), int(pos)) : wsn::wgrad_bound(L.cout, Kr, int(pos));
       part_floats = std::max<int64_t>(part_floats, int64_t(chunks) * L.cout * (Kr + 1));
     }
     A_(&part, part_floats);
@@ -379,17 +360,8 @@ struct ws_net {
     }
   }
 
-  // Positions per block of the direct weight gradient: a multiple of the stage.
-  // The chunks of a batch never exceed those of max_batch, which size the
-  // workspace.
-  int direct_chunk(const LayerSpec& L, int N, int* chunk) const {
-    const int Kr = L.cin * L.K, KT = &L == &layers.front() ? 1 : L.K, Cin = Kr / KT;
-    const int tiles = ((Cin + 31) / 32) * ((L.cout + 127) / 128);
-    const int stages = (N + wsn::kDirP - 1) / wsn::kDirP;
-    const int most = std::min(stages, std::max(1, kDirectTarget / tiles));
-    *chunk = (stages + most - 1) / most * wsn::kDirP;
-    return (N + *chunk - 1) / *chunk;
-  }
+  // source channels of a layer's direct weight gradient
+  int wgrad_channels(const LayerSpec& L) const { return &L == &layers.front() ? L.cin * L.K : L.cin; }
 
   template <int KT>
   void wgrad_direct_k(const wsn::DirectWgradArgs& a, int chunks) {
@@ -405,9 +377,10 @@ struct ws_net {
     if (direct(L)) {
       const bool embed = &L == &layers.front();
       wsn::DirectWgradArgs a{};
-      const int chunks = direct_chunk(L, N, &a.chunk);
       a.M = L.cout;
-      a.Cin = embed ? Kr : L.cin;
+      a.Cin = wgrad_channels(L);
+      const wsn::Chunks c = wsn::direct_chunks(a.M, a.Cin, N);
+      a.chunk = c.chunk;
       a.N = N;
       a.Lpos = Lpos;
       a.D = D;
@@ -416,19 +389,18 @@ struct ws_net {
       a.patch = embed ? L.K : 1;
       a.dil = L.dil;
       a.part = part;
-      if (L.K == 3 && !embed) wgrad_direct_k<3>(a, chunks);
-      else wgrad_direct_k<1>(a, chunks);
-      wgrad_sum(L, chunks);
+      if (L.K == 3 && !embed) wgrad_direct_k<3>(a, c.count);
+      else wgrad_direct_k<1>(a, c.count);
+      wgrad_sum(L, c.count);
       return;
     }
     const wsn::Gather g = gather_of(L, src, n, false);
-    int chunk;
-    const int chunks = wgrad_chunks(L.cout, Kr, N, &chunk);
-    const wsn::WgradArgs a{L.cout, Kr, N, chunk, D, g, part};
+    const wsn::Chunks c = wsn::wgrad_chunks(L.cout, Kr, N);
+    const wsn::WgradArgs a{L.cout, Kr, N, c.chunk, D, g, part};
     const dim3 grid(unsigned((Kr + 1 + wsn::kTile - 1) / wsn::kTile), unsigned((L.cout + wsn::kTile - 1) / wsn::kTile),
-                    unsigned(chunks));
+                    unsigned(c.count));
     hipLaunchKernelGGL(wsn::k_wgrad, grid, dim3(wsn::kThreads), 0, stream, a);
-    wgrad_sum(L, chunks);
+    wgrad_sum(L, c.count);
   }
 
   void wgrad_sum(const LayerSpec& L, int chunks) {

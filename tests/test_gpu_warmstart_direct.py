@@ -51,3 +51,36 @@ def test_forward_and_gradient(cfgd, n):
                 pos = sl.stop
                 assert np.linalg.norm(g[sl] - gref[sl]) < 2e-4 * np.linalg.norm(gref[sl]), (shapes, s)
     net.close()
+
+
+@pytest.mark.parametrize("max_batch, n", [(600, 512), (600, 587), (1100, 1024)])
+def test_gradient_of_a_batch_below_max_batch(max_batch, n):
+    """Default network: batches that have more chunks than max_batch has, and
+    one with several stages to a chunk and a last chunk cut short.
+
+    Tolerance: rounding moves a gradient of these sizes by 5e-7 of its norm, a
+    ReLU input that changes sign by it by up to 8e-5 (an FP32 evaluation on the
+    CPU against the FP64 one), and a few of the 5 to 10 million inputs may do so:
+    1e-3.  A chunk left out or added twice would be 1/128 or more."""
+    import torch
+    from paper_2102_00514_amd import warmstart as W
+    cfgd = dict(window=64, patch=4, width=128, hidden=4, nx=5, ny=2)
+    net = W.WarmStartNet(W.config(max_batch=max_batch, **cfgd), stream=torch.cuda.current_stream().cuda_stream, seed=4)
+    rng = np.random.default_rng(n)
+    x = rng.uniform(-1, 1, (n, 4, 64)).astype(np.float32)
+    lab = (rng.standard_normal((n, 64, 5)) * 2 + 0.5).astype(np.float32)
+    idx = rng.permutation(n).astype(np.int32)
+    dx, dl, di = (torch.from_numpy(v).cuda() for v in (x, lab, idx))
+    g, loss = net.gradient(dx.data_ptr(), dl.data_ptr(), n, di.data_ptr(), n)
+    t64 = net.params().astype(np.float64)
+    ref, cache = onn.forward(t64, x[idx].astype(np.float64), cfgd)
+    tgt = onn.states_to_outputs(lab[idx].astype(np.float64), np.zeros(5), np.ones(5), cfgd)
+    assert abs(loss - onn.loss(ref, tgt)) < 1e-5 * onn.loss(ref, tgt)
+    gref = onn.backward(t64, cache, ref, tgt, cfgd)
+    pos = 0
+    for shapes in onn.layer_shapes(cfgd):
+        for s in shapes:
+            sl = slice(pos, pos + int(np.prod(s)))
+            pos = sl.stop
+            assert np.linalg.norm(g[sl] - gref[sl]) < 1e-3 * np.linalg.norm(gref[sl]), (shapes, s)
+    net.close()
