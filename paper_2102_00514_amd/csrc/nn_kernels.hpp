@@ -139,7 +139,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // go through LDS as they lie in memory, so that a tap is a shifted LDS read,
 // masked at the window's edges, and no index is divided per element (the
 // gather of k_conv cost more than its multiply-adds).  The weights are packed
-// in the order in which the lanes take them (k_pack_direct) and come straight
+// in the order in which the lanes take them (k_pack) and come straight
 // from the caches: through LDS they took the registers of a second block per CU.
 // 128 x 384 x 16,384: 77 us with k_conv, 30 to 34 here; bound by the
 // products (10 us at the card's FP32 matrix rate) and 33 MB of activations.
@@ -177,13 +177,7 @@ struct PackDirect {
 __host__ __device__ __forceinline__ int64_t direct_words(int M, int Cin, int KT) {
   return int64_t((M + 31) / 32) * 2 * KT * ((Cin + 15) / 16) * 256;
 }
-constexpr int kPackMost = 32;
-struct PackDirectArgs {
-  PackDirect layer[kPackMost];
-};
-// grid (blocks, layers)
-__global__ __launch_bounds__(256) void k_pack_direct(PackDirectArgs args) {
-  const PackDirect a = args.layer[blockIdx.y];
+__device__ __forceinline__ void pack_direct(const PackDirect& a) {
   const int64_t words = direct_words(a.M, a.Cin, a.KT);
   const int S = a.KT * ((a.Cin + 15) / 16);
   for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < words; i += int64_t(gridDim.x) * 256) {
@@ -720,7 +714,7 @@ __global__ void k_scatter(WindowTable tab, const float* o, int64_t w0, int n, in
 // of its 16-deep steps are stored side by side -- channel 16 h + 4 g + j of a
 // group of 32 sits at 8 g + 4 h + j (net_col) -- so that one 16-byte read
 // feeds both, of the LDS tile and of the weights, which are packed in the
-// order in which the lanes take them (k_pack_net).
+// order in which the lanes take them (k_pack).
 // ---------------------------------------------------------------------------
 constexpr int kNetP = 128;   // positions per block
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
@@ -739,25 +733,39 @@ __host__ __device__ __forceinline__ int64_t net_words(int M, int Kr) {
 // step s) is row 16 mt + l % 16, reduction index r = 32 s + 16 (e / 4) +
 // 4 (l / 16) + e % 4, zero past the matrix.  Reduction order: taps outermost
 // when tap_major (r = k cin + c), else r = c K + k.
-struct PackArgs {
+struct PackNet {
   const float* W;
   int M, cin, K, tap_major;
   short* out;
 };
-__global__ __launch_bounds__(256) void k_pack_net(PackArgs a) {
+__device__ __forceinline__ void pack_net(const PackNet& a) {
   const int Kr = a.cin * a.K, steps = net_steps(Kr);
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= net_words(a.M, Kr)) return;
-  const int e = int(i & 7), l = int(i >> 3) & 63;
-  const int64_t t = i >> 9;
-  const int s = int(t % steps), m = int(t / steps) * 16 + (l & 15);
-  const int r = 32 * s + 16 * (e >> 2) + 4 * (l >> 4) + (e & 3);
-  float v = 0.f;
-  if (m < a.M && r < Kr) {
-    const int c = a.tap_major ? r % a.cin : r / a.K, k = a.tap_major ? r / a.cin : r - c * a.K;
-    v = a.W[(int64_t(m) * a.cin + c) * a.K + k];
+  const int64_t words = net_words(a.M, Kr);
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < words; i += int64_t(gridDim.x) * 256) {
+    const int e = int(i & 7), l = int(i >> 3) & 63;
+    const int64_t t = i >> 9;
+    const int s = int(t % steps), m = int(t / steps) * 16 + (l & 15);
+    const int r = 32 * s + 16 * (e >> 2) + 4 * (l >> 4) + (e & 3);
+    float v = 0.f;
+    if (m < a.M && r < Kr) {
+      const int c = a.tap_major ? r % a.cin : r / a.K, k = a.tap_major ? r / a.cin : r - c * a.K;
+      v = a.W[(int64_t(m) * a.cin + c) * a.K + k];
+    }
+    a.out[i] = to_bf16(v);
   }
-  a.out[i] = to_bf16(v);
+}
+
+// Every packed copy of the weights in one launch, grid (blocks, n_direct + n_net).
+constexpr int kPackDirect = 32, kPackNet = 16;
+struct PackArgs {
+  PackDirect direct[kPackDirect];
+  PackNet net[kPackNet];
+  int n_direct, n_net;
+};
+__global__ __launch_bounds__(256) void k_pack(PackArgs a) {
+  const int i = blockIdx.y;
+  if (i < a.n_direct) pack_direct(a.direct[i]);
+  else pack_net(a.net[i - a.n_direct]);
 }
 
 struct NetArgs {

@@ -16,6 +16,8 @@ namespace {
 
 thread_local std::string g_create_error;
 
+constexpr int kMostLayers = 14;   // embedding, residual layers, head
+
 struct LayerSpec {
   int cout, cin, K, stride, dil, pad;
   int64_t w_off, b_off;
@@ -27,6 +29,7 @@ const char* check_config(const ws_config& c) {
   if (c.patch < 1 || c.window % c.patch != 0) return "patch must divide window";
   if ((c.window / c.patch) % 4 != 0) return "window / patch must be a multiple of 4";
   if (c.width < 1 || c.width > 4096) return "width must be in [1, 4096]";
+  static_assert(kMostLayers == 12 + 2, "the largest number of layers");
   if (c.hidden < 0 || c.hidden > 12) return "hidden must be in [0, 12]";
   if (c.nx < 1 || c.nx > 64) return "nx must be in [1, 64]";
   if (c.ny < 1 || c.ny > 32) return "ny must be in [1, 32]";
@@ -76,12 +79,10 @@ struct ws_net {
   int* bad_index = nullptr;   // set by the batch gather when an index is out of range
   short* wt16 = nullptr;      // BF16 weights packed for k_net_mfma: embedding, residual layers, head
   bool net_fused = false;     // the inference form runs k_net_mfma (C = 128 or 256, 128 % Lpos == 0)
-  bool net_packed = false;    // wt16 holds the current parameters
   // FP32 weights packed for k_conv_direct: of each layer for the forward pass,
   // then of each layer after the embedding for the backward one
   float* wt32 = nullptr;
   std::vector<float*> wt_fwd, wt_bwd;   // null: the layer does not run it
-  bool direct_packed = false;           // wt32 holds the current parameters
   int64_t part_floats = 0;
   int* win_track = nullptr;
   int* win_start = nullptr;
@@ -176,6 +177,10 @@ struct ws_net {
     if (e == hipSuccess) e = hipMemsetAsync(mu, 0, sizeof(float) * c.nx, stream);
     if (e == hipSuccess) e = hipMemsetAsync(bad_index, 0, sizeof(int), stream);
     if (e == hipSuccess) e = hipMemcpyAsync(sigma, ones.data(), sizeof(float) * c.nx, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) {
+      pack();
+      e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fail(WS_EDEVICE, hip_msg(e, "initialisation"));
     return WS_OK;
@@ -217,20 +222,29 @@ struct ws_net {
     return wsn::direct_words(p.M, p.Cin, p.KT);
   }
 
-  // packed copies of the weights for k_conv_direct, made again when they have changed
-  void pack_direct() {
-    if (direct_packed) return;
-    wsn::PackDirectArgs a{};
-    unsigned n = 0;
+  // The packed copies of the weights (wt32, wt16).  Queued by every call that
+  // changes the parameters, right behind the change: whatever is queued later,
+  // a replay of a captured call among it, finds the copies of the parameters it
+  // runs with, and no call has to know which parameters were packed last.
+  void pack() {
+    static_assert(2 * kMostLayers <= wsn::kPackDirect && kMostLayers <= wsn::kPackNet, "tables of k_pack");
+    wsn::PackArgs a{};
     for (int tr = 0; tr < 2; ++tr)
       for (size_t l = 0; l < layers.size(); ++l) {
         float* out = (tr ? wt_bwd : wt_fwd)[l];
         if (!out) continue;
-        a.layer[n] = pack_of(layers[l], tr != 0);
-        a.layer[n++].out = out;
+        a.direct[a.n_direct] = pack_of(layers[l], tr != 0);
+        a.direct[a.n_direct++].out = out;
       }
-    hipLaunchKernelGGL(wsn::k_pack_direct, dim3(64, n), dim3(256), 0, stream, a);
-    direct_packed = true;
+    if (net_fused) {
+      short* out = wt16;
+      for (size_t l = 0; l < layers.size(); ++l) {
+        const LayerSpec& L = layers[l];
+        a.net[a.n_net++] = {theta + L.w_off, L.cout, L.cin, L.K, l > 0 ? 1 : 0, out};
+        out += wsn::net_words(L.cout, L.cin * L.K);
+      }
+    }
+    hipLaunchKernelGGL(wsn::k_pack, dim3(64, unsigned(a.n_direct + a.n_net)), dim3(256), 0, stream, a);
   }
 
   // src as the layer's channels see it
@@ -268,7 +282,6 @@ struct ws_net {
   // xb [2 ny][n W] -> out [P nx][n L]; keeps every activation for the backward pass
   void forward(int n) {
     const int Hn = cfg.hidden;
-    pack_direct();
     wsn::DirectArgs e = direct_args(layers[0], xb, n, false);
     e.out = H[0];
     conv_direct<wsn::kEpiRelu>(layers[0], e);
@@ -313,23 +326,8 @@ struct ws_net {
     conv_mfma<wsn::kEpiLinear>(a);
   }
 
-  // BF16 copies of the weights for k_net_mfma, made again when they have changed
-  void pack_net() {
-    if (net_packed) return;
-    short* out = wt16;
-    for (size_t l = 0; l < layers.size(); ++l) {
-      const LayerSpec& L = layers[l];
-      const int64_t words = wsn::net_words(L.cout, L.cin * L.K);
-      hipLaunchKernelGGL(wsn::k_pack_net, dim3(unsigned((words + 255) / 256)), dim3(256), 0, stream,
-                         wsn::PackArgs{theta + L.w_off, L.cout, L.cin, L.K, l > 0 ? 1 : 0, out});
-      out += words;
-    }
-    net_packed = true;
-  }
-
   // trajectory of every planned window through k_net_mfma (no workspace)
   void trajectory_fused(const double* d_y, double* d_mean) {
-    pack_net();
     const LayerSpec &LE = layers.front(), &LH = layers.back();
     wsn::NetArgs a{};
     a.tab = table();
@@ -547,10 +545,13 @@ ws_status ws_set_params(ws_t h, const float* params, int64_t n) {
   for (int64_t i = 0; i < n; ++i)
     if (!std::isfinite(params[i])) return h->fail(WS_EINVAL, "params must be finite");
   hipError_t e = hipMemcpyAsync(h->theta, params, sizeof(float) * n, hipMemcpyHostToDevice, h->stream);
+  if (e == hipSuccess) {
+    h->pack();
+    e = hipGetLastError();
+  }
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_m, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipMemsetAsync(h->adam_v, 0, sizeof(float) * n, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  h->net_packed = h->direct_packed = false;
   if (e != hipSuccess) return h->fail(WS_EDEVICE, hip_msg(e, "parameter upload"));
   h->step = 0;
   return WS_OK;
@@ -659,7 +660,7 @@ ws_status ws_train_step(ws_t h, const float* d_x, const float* d_lab, int64_t n_
   hipLaunchKernelGGL(wsn::k_adam, dim3(unsigned((h->n_params + 255) / 256)), dim3(256), 0, h->stream, h->theta,
                      static_cast<const float*>(h->grad), h->adam_m, h->adam_v, h->n_params, opt->lr, opt->beta1,
                      opt->beta2, opt->eps, c1, c2);
-  h->net_packed = h->direct_packed = false;
+  h->pack();
   ws_status s = launch_status(h, "training step");
   if (s != WS_OK || !loss_out) return s;
   const hipError_t e = hipMemcpyAsync(loss_out, h->loss, sizeof(float), hipMemcpyDeviceToHost, h->stream);
