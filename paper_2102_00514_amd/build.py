@@ -30,6 +30,19 @@ HIP_FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
+# Units with values of 32 bits: no vectorisation of scalar code.  Without packed
+# instructions it gains nothing, and this compiler (clang 22, ROCm 7.2) loses
+# copies of the pairs it makes: in the loop in which a lane folds its elements,
+# k_scan_up and k_scan_single (64 lanes) of SqrtSmootherOp<5, float> never moved
+# four entries of E to the registers that the products read, and FP32 in the
+# square-root form gave NaN past 2048 tiles.  tests/test_device_code.py looks
+# for such copies.  FP64 makes no such pairs and keeps its code.
+FP32_FLAGS = ["-fno-slp-vectorize"]
+
+
+def unit_flags(unit: str):
+    return HIP_FLAGS + (FP32_FLAGS if unit.endswith("_f32.hip") or unit == "warmstart.hip" else [])
+
 
 def sources():
     return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".hpp"))] + \
@@ -43,7 +56,7 @@ def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
     procs = []
     for unit in UNITS:
         obj = os.path.join(objdir, unit.replace(".hip", ".o"))
-        cmd = [HIPCC, *HIP_FLAGS, *extra, "-I", os.path.join(ROOT, "include"), "-c", "-o", obj,
+        cmd = [HIPCC, *unit_flags(unit), *extra, "-I", os.path.join(ROOT, "include"), "-c", "-o", obj,
                os.path.join(CSRC, unit)]
         if verbose:
             print(" ".join(cmd), flush=True)

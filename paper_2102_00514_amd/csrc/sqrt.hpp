@@ -106,7 +106,8 @@ PKS_DEV void tria_lower(R (&X)[M][M], R (&T)[M][M], R (&L)[M][M]) {
   PKS_UNROLL for (int i = 0; i < M; ++i) PKS_UNROLL for (int j = 0; j < M; ++j) L[i][j] = D[i][j];
 }
 
-// L = tria([X, T]), T lower triangular.  FP32 keeps the general form.
+// L = tria([X, T]), T lower triangular.  FP32 keeps the general form, equal to
+// the shorter one bit for bit, whose gain has not been measured there.
 template <int N, typename R>
 PKS_DEV void tria_cat(R (&X)[N][N], const R (&T)[N][N], R (&L)[N][N]) {
   if constexpr (sizeof(R) == 8) {

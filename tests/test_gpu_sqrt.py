@@ -265,3 +265,20 @@ def test_noise_free_component_limits(B):
     for form in ("covariance", "sqrt"):
         with pytest.raises(B.SmootherError, match="Q must be symmetric"):
             B.Smoother(bad, form=form)
+
+
+@pytest.mark.parametrize("tiles, tracks", [(2048, 1), (2049, 1), (2188, 1), (2600, 3)])
+def test_fp32_tile_levels(B, tiles, tracks):
+    """FP32 on both sides of the 2048 tiles that one block scans; past them the
+    tile aggregates go through levels of 64-lane blocks.  One iteration from the
+    prior against FP64 on the sequential path; a CPU evaluation in FP32 with the
+    same tree is 1.2e-5 (means) and 7.2e-5 (covariances) off at 140,000 steps."""
+    T = tiles * 64 // tracks - 1
+    pb = wl.ct_bearings(T, seed=1) if tracks == 1 else \
+        wl.concat_tracks([wl.ct_bearings(T - 5 * i, seed=1 + i) for i in range(tracks)], "levels")
+    with B.Smoother(pb, n_iter=1, lin="taylor", form="sqrt", precision="f32", tile_lanes=64, lane_slots=1) as sm:
+        assert sm.schedule()[2] == tiles
+        sm.iterate(1)
+        mean, cov = sm.result()
+    ref = run_gpu(B, pb, 1, scan="sequential")
+    assert max(errors(mean, cov, ref[0], ref[1])) < TOL32_FACTOR_LONG
