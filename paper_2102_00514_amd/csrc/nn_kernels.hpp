@@ -779,9 +779,14 @@ struct NetArgs {
   const float* br;               // bias of the first residual layer; the next one's br_stride later
   int64_t br_stride;
   const float *mu, *sigma;
+  const float* h0;               // !kEmbed: output of the embedding [C][n Lpos]
+  float* h1;                     // !kHead: takes the output of the last residual layer
 };
 
-template <int C>
+// Without kEmbed the embedding's output is read, without kHead the last layer's
+// is written (variants: with both forms in one kernel its registers spill, 422 us
+// instead of 375 for 32,768 windows).
+template <int C, bool kEmbed, bool kHead>
 __global__ __launch_bounds__(256, C == 128 ? 2 : 1) void k_net_mfma(NetArgs a) {
   static_assert(C % 128 == 0, "whole 32-row pairs of tiles per wave");
   constexpr int RT = C / 64;     // 16-row tiles per wave
@@ -835,49 +840,62 @@ __global__ __launch_bounds__(256, C == 128 ? 2 : 1) void k_net_mfma(NetArgs a) {
       }
   };
 
-  // embedding, in column blocks of C of its reduction (one for 2 ny P <= C)
-  const int Kr = 2 * a.ny * a.P, se = net_steps(Kr);
+  // embedding: its output, or formed here
   int row[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) row[j] = 16 * j + lr;
-  clear();
-  for (int kb = 0; kb < Kr; kb += C) {
-    const int cols = min(C, 32 * (se - kb / 32));
-    if (kb > 0) __syncthreads();
-    // columns past the reduction of the last step
-    for (int e = t; e < kNetP * 32; e += 256) {
-      const int c = cols - 32 + (e & 31);
-      if (kb + c >= Kr) Hs[e >> 5][net_col(c)] = 0;
-    }
-    const int per = a.ny * a.P;
-    for (int e = t; e < kNetP * per; e += 256) {
-      const int p = e / per, q = e - p * per, s = q % a.ny, k = q / a.ny;
-      const int c0 = 2 * s * a.P + k - kb, c1 = c0 + a.P;   // sine, cosine columns
-      float sf = 0.f, cf = 0.f;
-      if (p0 + p < N) {
-        const int64_t w = a.w0 + (p0 + p) / a.Lpos;
-        const int tr = a.tab.track[w];
-        const int64_t m0 = a.tab.meas_off[tr], T = a.tab.meas_off[tr + 1] - m0;
-        const int64_t st = min(int64_t(a.tab.start[w]) + ((p0 + p) % a.Lpos) * a.P + k, T);
-        double sv, cv;
-        sincos(a.y[(m0 + st - 1) * a.ny + s], &sv, &cv);
-        sf = float(sv);
-        cf = float(cv);
+  if constexpr (!kEmbed) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float* src = a.h0 + ((wv * RT + i) * 16 + 4 * g + q) * N + p0;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) h[i][j][q] = p0 + row[j] < N ? src[row[j]] : 0.f;
       }
-      if (c0 >= 0 && c0 < C) Hs[p][net_col(c0)] = to_bf16(sf);
-      if (c1 >= 0 && c1 < C) Hs[p][net_col(c1)] = to_bf16(cf);
+  } else {
+    // column blocks of C of the reduction, of whole (sine, cosine) pairs: one
+    // block, or 2 P divides C
+    const int Kr = 2 * a.ny * a.P, se = net_steps(Kr);
+    clear();
+    for (int kb = 0; kb < Kr; kb += C) {
+      const int cols = min(C, 32 * (se - kb / 32)), per = min(C, Kr - kb) / 2;
+      const int s0 = kb / (2 * a.P), ns = per / a.P;   // first sensor of the block, sensors in it
+      if (kb > 0) __syncthreads();
+      // columns past the reduction of the last step
+      for (int e = t; e < kNetP * 32; e += 256) {
+        const int c = cols - 32 + (e & 31);
+        if (kb + c >= Kr) Hs[e >> 5][net_col(c)] = 0;
+      }
+      for (int e = t; e < kNetP * per; e += 256) {
+        const int p = e / per, q = e - p * per, s = q % ns, k = q / ns;
+        const int c0 = 2 * s * a.P + k, c1 = c0 + a.P;   // sine, cosine columns
+        float sf = 0.f, cf = 0.f;
+        if (p0 + p < N) {
+          const int64_t w = a.w0 + (p0 + p) / a.Lpos;
+          const int tr = a.tab.track[w];
+          const int64_t m0 = a.tab.meas_off[tr], T = a.tab.meas_off[tr + 1] - m0;
+          const int64_t st = min(int64_t(a.tab.start[w]) + ((p0 + p) % a.Lpos) * a.P + k, T);
+          double sv, cv;
+          sincos(a.y[(m0 + st - 1) * a.ny + s0 + s], &sv, &cv);
+          sf = float(sv);
+          cf = float(cv);
+        }
+        Hs[p][net_col(c0)] = to_bf16(sf);
+        Hs[p][net_col(c1)] = to_bf16(cf);
+      }
+      __syncthreads();
+      product(a.we, se, kb / 32, cols / 32, row);
     }
-    __syncthreads();
-    product(a.we, se, kb / 32, cols / 32, row);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float b = a.be[(wv * RT + i) * 16 + 4 * g + q];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) h[i][j][q] = fmaxf(acc[i][j][q] + b, 0.f);
+      }
   }
-#pragma unroll
-  for (int i = 0; i < RT; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float b = a.be[(wv * RT + i) * 16 + 4 * g + q];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) h[i][j][q] = fmaxf(acc[i][j][q] + b, 0.f);
-    }
   __syncthreads();
   publish();
   __syncthreads();
@@ -909,6 +927,19 @@ __global__ __launch_bounds__(256, C == 128 ? 2 : 1) void k_net_mfma(NetArgs a) {
     __syncthreads();
     publish();
     __syncthreads();
+  }
+
+  if constexpr (!kHead) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float* dst = a.h1 + ((wv * RT + i) * 16 + 4 * g + q) * N + p0;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          if (p0 + 16 * j + lr < N) dst[16 * j + lr] = h[i][j][q];
+      }
+    return;
   }
 
   // head: each wave takes 32 positions and every output row; step k of a track

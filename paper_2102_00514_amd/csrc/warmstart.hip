@@ -306,27 +306,72 @@ struct ws_net {
   // The inference form of the products layer by layer (BF16 operands on the
   // matrix cores, FP32 accumulation), where k_net_mfma does not apply
   void forward_mfma(int n) {
-    const int N = n * Lpos, Hn = cfg.hidden;
-    auto args = [&](const LayerSpec& L, const float* src) {
-      return wsn::ConvArgs{L.cout, L.cin * L.K, N, theta + L.w_off, 0, theta + L.b_off, gather_of(L, src, n, false),
-                           nullptr, nullptr, nullptr, nullptr};
-    };
-    wsn::ConvArgs a = args(layers[0], xb);
-    a.out = H[0];
-    conv_mfma<wsn::kEpiRelu>(a);
+    const int Hn = cfg.hidden;
+    embed_mfma(n);
     for (int l = 1; l <= Hn; ++l) {
-      a = args(layers[l], H[l - 1]);
+      wsn::ConvArgs a = args_mfma(layers[l], H[l - 1], n);
       a.out = A[l];
       a.out2 = H[l];
       a.in2 = H[l - 1];
       conv_mfma<wsn::kEpiResidual>(a);
     }
-    a = args(layers[Hn + 1], H[Hn]);
+    head_mfma(n);
+  }
+  wsn::ConvArgs args_mfma(const LayerSpec& L, const float* src, int n) const {
+    return {L.cout, L.cin * L.K, n * Lpos, theta + L.w_off, 0, theta + L.b_off, gather_of(L, src, n, false),
+            nullptr, nullptr, nullptr, nullptr};
+  }
+  void embed_mfma(int n) {
+    wsn::ConvArgs a = args_mfma(layers[0], xb, n);
+    a.out = H[0];
+    conv_mfma<wsn::kEpiRelu>(a);
+  }
+  void head_mfma(int n) {
+    wsn::ConvArgs a = args_mfma(layers.back(), H[cfg.hidden], n);
     a.out = out;
     conv_mfma<wsn::kEpiLinear>(a);
   }
 
-  // trajectory of every planned window through k_net_mfma (no workspace)
+  // network inputs of planned windows w0 .. w0 + n - 1 into xb
+  void features(const double* d_y, int64_t w0, int n) {
+    const int64_t cnt = int64_t(n) * cfg.window;
+    hipLaunchKernelGGL(wsn::k_features, dim3(unsigned((cnt + 255) / 256)), dim3(256), 0, stream, table(), d_y, cfg.ny,
+                       cfg.window, w0, n, 1, xb);
+  }
+  // states of those windows from their outputs
+  void scatter(double* d_mean, int64_t w0, int n) {
+    const int64_t cnt = int64_t(n) * cfg.window;
+    hipLaunchKernelGGL(wsn::k_scatter, dim3(unsigned((cnt + 255) / 256)), dim3(256), 0, stream, table(),
+                       static_cast<const float*>(out), w0, n, cfg.window, cfg.patch, cfg.nx,
+                       static_cast<const float*>(mu), static_cast<const float*>(sigma), d_mean);
+  }
+
+  template <int C>
+  void net_mfma(const wsn::NetArgs& a, dim3 grid, bool wide_in, bool wide_out) {
+    if (wide_in && wide_out)
+      hipLaunchKernelGGL((wsn::k_net_mfma<C, false, false>), grid, dim3(256), 0, stream, a);
+    else if (wide_in)
+      hipLaunchKernelGGL((wsn::k_net_mfma<C, false, true>), grid, dim3(256), 0, stream, a);
+    else if (wide_out)
+      hipLaunchKernelGGL((wsn::k_net_mfma<C, true, false>), grid, dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL((wsn::k_net_mfma<C, true, true>), grid, dim3(256), 0, stream, a);
+  }
+
+  // Trajectory of every planned window through k_net_mfma.  A block of it works
+  // through all columns of the embedding and all rows of the head of its 128
+  // positions.  Where blocks are few and columns or rows many, these two are
+  // launches of their own, which spread over rows and columns too, with their
+  // operands in the workspace.
+  // Embedding: in the kernel with one block of `width` columns, or, when the
+  // blocks fill the chip, with more of them (2 sensors, patches of 64, 512 blocks:
+  // 233 us, 323 with a launch of its own; 16 sensors, patches of 16: 4 blocks 158
+  // and 120, 128 blocks 178 and 168); never when a sensor's sines and cosines would
+  // fall into different blocks (2 sensors, 4096 steps in 4 patches, 4 blocks: 23.3
+  // ms a call when every column block formed all of them, 0.58 now).
+  // Head: 0.19 us a row in the kernel whatever the blocks, 15 us and 1.8 ns a row
+  // and block outside (320 rows: 4 blocks 120 and 79 us a call, 128 blocks 138 and
+  // 166), equal where rows (104 - blocks) = 8300.
   void trajectory_fused(const double* d_y, double* d_mean) {
     const LayerSpec &LE = layers.front(), &LH = layers.back();
     wsn::NetArgs a{};
@@ -348,13 +393,27 @@ struct ws_net {
     a.br_stride = layers[1].weights() + layers[1].cout;
     a.mu = mu;
     a.sigma = sigma;
-    constexpr int64_t kMost = int64_t(1) << 20;   // windows per launch (grid size)
-    for (int64_t w0 = 0; w0 < n_windows; w0 += kMost) {
+    const int64_t blocks = (n_windows * Lpos + wsn::kNetP - 1) / wsn::kNetP;
+    const bool wide_in = LE.cin * LE.K > cfg.width && (blocks < 256 || cfg.width % (2 * cfg.patch) != 0);
+    const bool wide_out = LH.cout * (104 - blocks) > 8300;
+    // windows per launch: the workspace, else the grid size
+    const int64_t most = wide_in || wide_out ? cfg.max_batch : int64_t(1) << 20;
+    for (int64_t w0 = 0; w0 < n_windows; w0 += most) {
       a.w0 = w0;
-      a.n = std::min(kMost, n_windows - w0);
+      a.n = std::min(most, n_windows - w0);
+      if (wide_in) {
+        features(d_y, w0, int(a.n));
+        embed_mfma(int(a.n));
+        a.h0 = H[0];
+      }
+      if (wide_out) a.h1 = H[cfg.hidden];
       const dim3 grid(unsigned((a.n * Lpos + wsn::kNetP - 1) / wsn::kNetP));
-      if (cfg.width == 128) hipLaunchKernelGGL(wsn::k_net_mfma<128>, grid, dim3(256), 0, stream, a);
-      else hipLaunchKernelGGL(wsn::k_net_mfma<256>, grid, dim3(256), 0, stream, a);
+      if (cfg.width == 128) net_mfma<128>(a, grid, wide_in, wide_out);
+      else net_mfma<256>(a, grid, wide_in, wide_out);
+      if (wide_out) {
+        head_mfma(int(a.n));
+        scatter(d_mean, w0, int(a.n));
+      }
     }
   }
 
@@ -713,18 +772,12 @@ static ws_status trajectory(ws_t h, const double* d_y, double* d_mean, bool mfma
     h->trajectory_fused(d_y, d_mean);
     return launch_status(h, "trajectory");
   }
-  const int W = h->cfg.window;
   for (int64_t w0 = 0; w0 < h->n_windows; w0 += h->cfg.max_batch) {
     const int nb = int(std::min<int64_t>(h->cfg.max_batch, h->n_windows - w0));
-    const int64_t cnt = int64_t(nb) * W;
-    const dim3 grid(unsigned((cnt + 255) / 256));
-    hipLaunchKernelGGL(wsn::k_features, grid, dim3(256), 0, h->stream, h->table(), d_y, h->cfg.ny, W, w0, nb, 1,
-                       h->xb);
+    h->features(d_y, w0, nb);
     if (mfma) h->forward_mfma(nb);
     else h->forward(nb);
-    hipLaunchKernelGGL(wsn::k_scatter, grid, dim3(256), 0, h->stream, h->table(), static_cast<const float*>(h->out),
-                       w0, nb, W, h->cfg.patch, h->cfg.nx, static_cast<const float*>(h->mu),
-                       static_cast<const float*>(h->sigma), d_mean);
+    h->scatter(d_mean, w0, nb);
   }
   return launch_status(h, "trajectory");
 }
