@@ -31,15 +31,6 @@ constexpr int kScanB = 64;        // lanes per scan tile (one wavefront)
 constexpr int kLevelK = 2;        // positions per lane below the top level
 constexpr int kTopMaxK = 8;       // a single block scans at most kTopB * kTopMaxK tile aggregates
 constexpr int kTopB = 256;        // lanes of the single-block scan of the tile aggregates
-// Up to two aggregates a lane the single block is the shortest chain; past
-// that its folds, combines of whole elements by one block, cost more than the
-// two launches of a level of 64-lane blocks (2040 tiles, FP64: filtering
-// 109 us in one block, 44 us in levels; smoothing 78 and 24 us).
-// The levels need scratch: under a memory limit the single block stays as far
-// as it goes; so it does in FP32, whose results move with the shape of the
-// tree, and in the square-root form, where the gain has not been measured.
-constexpr int kTopOneK = 2;
-
 struct ScanLevel {
   int64_t m;
   int K;
@@ -100,6 +91,17 @@ class Engine final : public EngineBase {
   using FOp = FilterOp<N, R>;
   using SOp = SmootherOp<N, R>;
   using Rows = LinRows<Model, R>;
+  // Up to so many aggregates a lane the single block scans the tiles.  Past
+  // that its folds, combines of whole elements by one block, cost more than the
+  // two launches of a level of 64-lane blocks, the sooner the larger the
+  // element (FP64, us an iteration in one block and in levels): n = 5, 700 tiles
+  // 160 and 165, 900 tiles 184 and 175, 2047 tiles 385 and 262; n = 3, 800 tiles 80
+  // and 83, 1024 tiles 90 and 90, 1536 tiles 130 and 115; n = 1, 1536 tiles 66.5 and
+  // 68.2, 2047 tiles 84.3 and 80.2.
+  // The levels need scratch: under a memory limit the single block stays as far
+  // as it goes; so it does in FP32, whose results move with the shape of the
+  // tree, and in the square-root form, where the gain has not been measured.
+  static constexpr int kTopOneK = N >= 5 ? 3 : N > 1 ? 4 : 7;
 
   sm_status setup(const sm_problem& pb, hipStream_t st) override {
     stream = st;

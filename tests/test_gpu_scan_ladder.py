@@ -79,3 +79,14 @@ def test_square_root_form(B, T):
     for got, want in ((m, ms), (c.reshape(len(m), -1), cs.reshape(len(m), -1))):
         scale = np.abs(want).max(axis=0)
         assert np.all(np.abs(got - want) <= TOL * scale)
+
+
+@pytest.mark.parametrize("nx, tiles", [(5, 768), (5, 769), (3, 1024), (3, 1025), (1, 1792), (1, 1793)])
+def test_last_tiles_of_one_block(B, nx, tiles):
+    """The last number of tiles that one block scans without a memory limit, and
+    the first that goes through levels, by the size of the state."""
+    T = tiles * 64 - 9
+    pb = wl.ct_bearings(T, seed=nx) if nx == 5 else wl.linear_gaussian(nx, {1: 1, 3: 2}[nx], T, seed=nx)
+    with B.Smoother(pb, n_iter=1, lin="taylor", tile_lanes=64, lane_slots=1) as sm:
+        assert sm.schedule()[2] == tiles
+    _compare(B, pb, lin="taylor", tile_lanes=64, lane_slots=1)
