@@ -130,20 +130,20 @@ PKS_DEV bool ladder_source(int s, int wl, int& src) {
   return qrow >= 2;
 }
 
-// Elements a block of B lanes keeps in LDS for block_ladder: every lane's and
-// one total per wavefront (kInLds), or the totals only.
+// Elements a block of B lanes keeps in LDS for block_ladder: every lane's
+// (kInLds), or one total per wavefront.
 template <class Op, int B>
 constexpr int ladder_elems() {
-  return Op::kInLds ? B + (B > 64 ? B / 64 : 0) : B / 64;
+  return Op::kInLds ? B : B / 64;
 }
 
 // Inclusive scan of the B lane values of a block.  Scan position q = lane
 // (FWD) or B-1-lane (reverse).  Inside a wavefront the six Kogge-Stone steps
 // need no barrier; across wavefronts (B > 64) each wavefront's total goes
-// through LDS.  lds holds ladder_elems() elements, entry-major: first the
-// lanes' (kInLds, 64 per wavefront and entry), then the totals (row stride
-// B/64).  On exit v is the inclusive prefix at q and, when want_ex and has_ex
-// (q > 0), ex the exclusive one.
+// through LDS.  lds holds ladder_elems() elements, entry-major: the lanes'
+// (kInLds, 64 per wavefront and entry) or the totals (row stride B/64).  On
+// exit v is the inclusive prefix at q and, when want_ex and has_ex (q > 0), ex
+// the exclusive one.
 // Invalid lanes must form a suffix of the scan order: no valid lane reads
 // their values.  A wavefront whose lanes are all invalid passes active =
 // false (wavefront-uniform): it skips its combines and only takes part in the
@@ -155,9 +155,9 @@ constexpr int ladder_elems() {
 // A block of one wavefront per SIMD is bound by its longest chain of combines
 // (n = 5, FP64: 3.1 us a filtering combine, of which 2.1 us are its 1190
 // multiply-adds; 3.7 us with the operands in registers and lane moves between
-// them).  Four wavefronts without exclusive prefixes therefore join their
-// totals in two rounds, pairs first, instead of the last wavefront folding
-// three totals in turn: eight combines instead of nine.  One track, FP64:
+// them).  Four wavefronts in LDS therefore join their totals in two rounds,
+// pairs first, instead of the last wavefront folding three totals in turn:
+// eight combines instead of nine.  One track, FP64:
 // forward_up 43.6 us before, 39.5 us now at T = 32768; 37.5 and 31.1 us at
 // T = 100, where two of the four wavefronts hold padding only.  FP32 keeps
 // lane moves and the order of the fold, so that its results stay what they
@@ -166,13 +166,12 @@ template <class Op, int B, bool FWD, typename R>
 PKS_DEV void block_ladder(R* lds, typename Op::Elem& v, typename Op::Elem& ex, bool& has_ex, bool active = true,
                           bool want_ex = true, int first_wave = 0, int nvalid = 64) {
   constexpr int NW = B / 64;
-  static_assert(B % 64 == 0, "whole wavefronts");
+  static_assert(B % 64 == 0 && (!Op::kInLds || NW == 1 || NW == 4), "whole wavefronts; in LDS one or four");
   const int pl = int(threadIdx.x), wl = pl & 63, w = pl >> 6;
   const int qw = FWD ? wl : 63 - wl;        // scan position inside the wavefront
   const int qwave = FWD ? w : NW - 1 - w;   // scan position of the wavefront
   constexpr size_t kRegion = size_t(Op::kElemWords) * 64;
   R* const mine = lds + (Op::kInLds ? w * kRegion : 0);
-  R* const totals = lds + (Op::kInLds ? NW * kRegion : 0);
   has_ex = false;
   if (active) {
     if constexpr (Op::kInLds) {
@@ -208,30 +207,39 @@ PKS_DEV void block_ladder(R* lds, typename Op::Elem& v, typename Op::Elem& ex, b
     }
   }
   if constexpr (Op::kInLds && NW == 4) {
-    if (!want_ex) {
-      constexpr int kLast = FWD ? 63 : 0;   // lane of a wavefront's last position
-      auto region = [&](int q) { return lds + (FWD ? q : NW - 1 - q) * kRegion; };
-      __syncthreads();
-      if (active && (qwave & 1) && qwave > first_wave) Op::combine_at(mine, wl, region(qwave - 1), kLast);
-      __syncthreads();
-      if (active && qwave >= 2 && first_wave < 2) Op::combine_at(mine, wl, region(1), kLast);
-      order_lds();
-      if (active) Op::load(mine, 64, wl, v);
-      return;
+    constexpr int kLast = FWD ? 63 : 0;   // lane of a wavefront's last position
+    auto region = [&](int q) { return lds + (FWD ? q : NW - 1 - q) * kRegion; };
+    __syncthreads();
+    if (active && (qwave & 1) && qwave > first_wave) Op::combine_at(mine, wl, region(qwave - 1), kLast);
+    __syncthreads();
+    if (active && qwave >= 2 && first_wave < 2) Op::combine_at(mine, wl, region(1), kLast);
+    if (want_ex) __syncthreads();
+    else order_lds();
+    if (!active) return;
+    Op::load(mine, 64, wl, v);
+    has_ex = want_ex && (qw > 0 || qwave > first_wave);
+    if (has_ex) {
+      if (qw > 0) Op::load(mine, 64, FWD ? wl - 1 : wl + 1, ex);
+      else Op::load(region(qwave - 1), 64, kLast, ex);
     }
+    return;
   }
   if constexpr (Op::kInLds) {
-    if (active) Op::load(mine, 64, wl, v);
+    if (!active) return;
+    Op::load(mine, 64, wl, v);
+    has_ex = want_ex && qw > 0;
+    if (has_ex) Op::load(mine, 64, FWD ? wl - 1 : wl + 1, ex);
+    return;
   }
   typename Op::Elem wp;   // total of the wavefronts before this one (qwave > first_wave)
   if constexpr (NW > 1) {
-    if (active && qw == 63) Op::store(totals, NW, qwave, v);
+    if (active && qw == 63) Op::store(lds, NW, qwave, v);
     __syncthreads();
     if (active && qwave > first_wave) {
-      Op::load(totals, NW, first_wave, wp);
+      Op::load(lds, NW, first_wave, wp);
       for (int k = first_wave + 1; k < qwave; ++k) {
         typename Op::Elem t, r;
-        Op::load(totals, NW, k, t);
+        Op::load(lds, NW, k, t);
         Op::combine(wp, t, r);
         wp = r;
       }
@@ -241,19 +249,10 @@ PKS_DEV void block_ladder(R* lds, typename Op::Elem& v, typename Op::Elem& ex, b
     }
   }
   if (!active || !want_ex) return;
-  // the previous lane's inclusive prefix
+  // the previous lane's inclusive prefix: wave_shr:1 / wave_shl:1
   has_ex = qw > 0;
-  if constexpr (Op::kInLds) {
-    if constexpr (NW > 1) {
-      Op::store(mine, 64, wl, v);
-      order_lds();
-    }
-    if (has_ex) Op::load(mine, 64, FWD ? wl - 1 : wl + 1, ex);
-  } else {
-    // wave_shr:1 / wave_shl:1
-    if constexpr (FWD) Op::move(v, DppMove<0x138, 0xf>{}, ex);
-    else Op::move(v, DppMove<0x130, 0xf>{}, ex);
-  }
+  if constexpr (FWD) Op::move(v, DppMove<0x138, 0xf>{}, ex);
+  else Op::move(v, DppMove<0x130, 0xf>{}, ex);
   if constexpr (NW > 1) {
     if (qw == 0 && qwave > first_wave) {
       ex = wp;

@@ -90,3 +90,11 @@ def test_last_tiles_of_one_block(B, nx, tiles):
     with B.Smoother(pb, n_iter=1, lin="taylor", tile_lanes=64, lane_slots=1) as sm:
         assert sm.schedule()[2] == tiles
     _compare(B, pb, lin="taylor", tile_lanes=64, lane_slots=1)
+
+
+@pytest.mark.parametrize("slots", (2, 4))
+@pytest.mark.parametrize("T", (3, 130, 256, 700, 256 * 4 * 3 - 2))
+def test_exclusive_prefixes_of_four_wavefronts(B, slots, T):
+    """Several slots a lane: the lanes' exclusive prefixes across wavefronts, last
+    wavefronts that hold padding among them."""
+    _compare(B, wl.ct_bearings(T, seed=500 + T), lin="taylor", tile_lanes=256, lane_slots=slots)
