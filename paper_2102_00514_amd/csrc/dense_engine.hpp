@@ -186,7 +186,8 @@ class DenseEngine final : public EngineBase {
   // chip, more slots per chunk mean fewer combines and carries above level 0.
   // Unscented FP64, ms per iteration with 1, 2, 4, 8 slots: S = 256: 0.398 0.402
   // 0.435 0.564; 2001: 0.626 0.574 0.620 0.734; 4001: 0.845 0.764 0.732 0.842;
-  // 8001: 1.207 1.056 1.013 1.003; 32,001: - - 2.452 2.463.  FP32 keeps eight: its
+  // 32,001: - - 2.452 2.463.  From 8000 slots on four and eight take turns (8001:
+  // 1.017 0.991; 10,001: 1.109 1.119; 12,001: 1.216 1.151).  FP32 keeps eight: its
   // results move by up to 2e-5 with the shape of the scan tree.  Smaller chunks
   // need more aggregates; under a cap on device memory the plan stays the
   // smaller one.
