@@ -15,7 +15,7 @@ Other workloads (one JSON line each): c3, 4096 ragged tracks with T_i ~ U{100..8
 (cubature; steps = sum of T_i per iteration); c5, four stacked targets (nx = 20,
 eight bearings, T = 2^16, unscented) on the wavefront-cooperative engine, whose
 roofline is FP64 arithmetic; c5batch, 256 such tracks with T_i ~ U{1024..65536}
-in one ragged batch (~8.5e6 slots, ~133 GB of device memory); c2sweep, T = 2^10..2^15 on the GPU parallel and
+in one ragged batch (~8.5e6 slots, 161 GB of device memory); c2sweep, T = 2^10..2^15 on the GPU parallel and
 sequential paths (FP64 and FP32) and the CPU oracle.  The learned warm-start
 comparison runs with c2.
 
@@ -76,8 +76,12 @@ def design_bytes_per_position(kernel: str, n: int, p: int, lin: str, word: int, 
     fe = n * n + 2 * n + 2 * s          # filtering element (A, b, C, eta, J)
     se = n * n + n + s                  # smoothing element (E, g, L)
     car = n + s                         # trajectory slot (mean, packed covariance)
-    tr = n * n + n + s                  # transition rows (F, c, Q') of the stored linearisation
-    lin_words = n * n + n + s + p * n + p + sp + p
+    # Stored linearisation: transition rows (F, c, Q') and measurement rows
+    # (H, d, R', ytil).  One coordinated-turn target in FP64 stores neither the
+    # turn rate's transition rows nor the columns a bearing does not read.
+    nf, nh = (n - 1, 2) if n == 5 and word == 8 else (n, n)
+    tr = nf * n + nf + nf * (nf + 1) // 2
+    lin_words = tr + p * nh + p + sp + p
     xin = n + (s if lin != "taylor" else 0)   # linearisation point (mean [+ covariance])
     # Filtering elements are never stored: the forward down-sweep builds them
     # again (K > 1) from the linearisation point (Taylor) or the stored
